@@ -122,13 +122,6 @@ thread_local int t_fail_after = -1;
 // Workgroups and merge mode of this thread's last k_pyramid launch; -1: none yet.
 thread_local int t_pyr_blocks = -1, t_pyr_merged = 0;
 
-// Alignment (16, 4 or 1 bytes) that every row start of an image has.
-int row_alignment(const uint8_t *p, int64_t stride)
-{
-    const uintptr_t v = (uintptr_t)p | (uintptr_t)stride;
-    return v % 16 == 0 ? 16 : (v % 4 == 0 ? 4 : 1);
-}
-
 // First chunk of each level within one image.  With `pairs`, level 0 counts
 // units of two rows by kPairWords words and level 1 none (its bitmaps come
 // from level 0's units).
@@ -184,7 +177,7 @@ bool level1_from_level0(const Geometry &g, int n, const LaunchTune &t)
 
 // Enqueues a launch set on s.  `ws` is 256-byte aligned; `zero` lists output
 // regions to clear first (taken by value, its free slots are used here).
-hipError_t enqueue_set(const PairSet &ps, const Geometry &g, int64_t stride, int align, int exclude,
+hipError_t enqueue_set(const PairSet &ps, const Geometry &g, int64_t stride, int exclude,
                        uint8_t *ws, SearchOutputs out, ZeroArgs zero, int cus, hipStream_t s,
                        bool bytemaps = false, const LaunchTune &t = LaunchTune())
 {
@@ -216,7 +209,6 @@ hipError_t enqueue_set(const PairSet &ps, const Geometry &g, int64_t stride, int
     }
     pa.stride = stride;
     pa.n = n;
-    pa.align = align;
     pa.skip_l1 = pairs;
     pa.g = g;
     e = launch_pyramid(pa, cus, s, t.pyr_pct, t.pyr_group_log2);
@@ -823,15 +815,11 @@ mtb_status align_units(const std::vector<BatchUnit> &u, int64_t rows, int32_t ex
         Geometry g;
         make_geometry(f.W, f.H, f.L, &g);
         PairSet ps;
-        int align = 16;
         for (int item : grp.items) {
             const BatchUnit &b = u[item];
             const int base = ps.n;
-            for (int i = 0; i < b.n; ++i) {
+            for (int i = 0; i < b.n; ++i)
                 ps.rgb[ps.n++] = b.img[i];
-                const int a = row_alignment(b.img[i], b.stride);
-                align = a < align ? a : align;
-            }
             for (int i = 0; i < b.n; ++i) {
                 if (i == b.ref)
                     continue;
@@ -854,7 +842,7 @@ mtb_status align_units(const std::vector<BatchUnit> &u, int64_t rows, int32_t ex
         else
             tune_lookup(key, &t);
         const int l = plan.lane[k];
-        e = enqueue_set(ps, g, f.stride, align, exclude_range, ws + l * plan.lane_bytes, out, z, cus,
+        e = enqueue_set(ps, g, f.stride, exclude_range, ws + l * plan.lane_bytes, out, z, cus,
                         lanes ? lanes->s[l] : s, false, t);
     }
     // Join every lane back into the caller's stream, also after a failed
@@ -1065,7 +1053,6 @@ mtb_status mtb_build_pyramid(const uint8_t *d_rgb, int32_t width, int32_t height
     a.pyr[0] = pyr;
     a.stride = row_stride;
     a.n = 1;
-    a.align = row_alignment(d_rgb, row_stride);
     a.g = g;
     return device_status(launch_pyramid(a, cus, s));
 }
@@ -1153,13 +1140,9 @@ mtb_status align_stack(const uint8_t *const *h_d_rgb, int32_t n, int32_t width, 
     const int ref = ref_index < 0 ? n / 2 : ref_index;
     if (ref >= n)
         return MTB_ERR_INVALID_ARG;
-    int align = 16;
-    for (int i = 0; i < n; ++i) {
+    for (int i = 0; i < n; ++i)
         if (!h_d_rgb[i])
             return MTB_ERR_INVALID_ARG;
-        const int ai = row_alignment(h_d_rgb[i], row_stride);
-        align = ai < align ? ai : align;
-    }
     const size_t need = bytemaps ? mtb_stack_bytemaps_workspace_bytes(n, width, height, levels)
                                  : mtb_stack_workspace_bytes(n, width, height, levels);
     if (workspace_bytes < need)
@@ -1201,7 +1184,7 @@ mtb_status align_stack(const uint8_t *const *h_d_rgb, int32_t n, int32_t width, 
         t = *shape;
     else if (!bytemaps)
         tune_lookup(tune_key(n, width, height, levels, row_stride), &t);
-    hipError_t e = enqueue_set(ps, g, row_stride, align, exclude_range, ws, out, z, cus, s, bytemaps, t);
+    hipError_t e = enqueue_set(ps, g, row_stride, exclude_range, ws, out, z, cus, s, bytemaps, t);
     if (e == hipSuccess && chained && n > 1)
         e = launch_chain(d_shifts, n, ref, s);
     return device_status(e);

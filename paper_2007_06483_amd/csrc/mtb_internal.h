@@ -76,10 +76,10 @@ struct PyramidArgs {
     int32_t n;               // images
     int32_t tiles_x, tiles_y;
     int32_t xcd_tiles;       // tiles of each XCD's contiguous share of the work
-    int32_t align;           // 16, 4 or 1: alignment every RGB row start is known to have
     int32_t merge;           // 1: histograms merged through per-XCD copies (see k_pyramid)
     int32_t group_log2;      // a workgroup takes 2^group_log2 consecutive tiles of a row at a time
     int32_t skip_l1;         // 1: level 1's gray is not stored (the bitmaps pass forms it from level 0)
+    int32_t pad_;
     Geometry g;
 };
 

@@ -44,13 +44,8 @@ __global__ __launch_bounds__(256) void k_zero(ZeroArgs a)
 
 // ---------------------------------------------------------------- pass 1
 
-// Ward's integer gray weights; they sum to 256 so the result fits a byte.
-__device__ __forceinline__ uint32_t gray3(uint32_t r, uint32_t g, uint32_t b)
-{
-    return (54u * r + 183u * g + 19u * b) >> 8;
-}
-
-// Gray of 4 interleaved RGB pixels held in 3 little-endian dwords
+// Ward's integer gray weights (54 R + 183 G + 19 B) >> 8; they sum to 256 so the
+// result fits a byte.  Gray of 4 interleaved RGB pixels held in 3 little-endian dwords
 // (R0 G0 B0 R1 | G1 B1 R2 G2 | B2 R3 G3 B3), with byte dot products.
 __device__ __forceinline__ void gray4(uint32_t a, uint32_t b, uint32_t c, uint32_t *g)
 {
@@ -89,21 +84,66 @@ constexpr int kHStride = 257;
 // Clang vector type, the operand type the nontemporal builtins accept.
 typedef uint32_t U32x4 __attribute__((ext_vector_type(4)));
 
-// Loads one lane's 4 rows x 48 bytes (16 pixels) of RGB with 16-byte loads;
-// rows at or below H read as zero.
-__device__ __forceinline__ void load_rgb16(const uint8_t *rgb, int64_t stride, int x0, int y0, int H,
-                                           uint4 (&q)[4][3])
+typedef uint32_t U32x2 __attribute__((ext_vector_type(2)));
+// The same four dwords at any byte address: a global load takes any alignment.
+typedef uint32_t U32x4u __attribute__((ext_vector_type(4), aligned(1)));
+typedef uint32_t U32u __attribute__((aligned(1)));
+
+// Loads one lane's 4 rows of RGB (16 pixels, 48 bytes, 12 dwords each), rows at
+// any byte alignment; rows past the last one read the last one again.  In the
+// last lane of a row that is no multiple of 16 pixels wide, dword k is loaded
+// from at most 4 bytes before the row's end (fill_rgb16 moves it into place),
+// so that no load leaves the row; dwords past the end hold no defined value,
+// nor does a lane past the row's end.
+__device__ __forceinline__ void load_rgb16(const uint8_t *rgb, int64_t stride, int x0, int y0, int W, int H,
+                                           uint32_t (&q)[4][12])
+{
+    const int nb = 3 * (W - x0);  // bytes from the lane's first pixel to the row's end
+    if (nb <= 0)
+        return;
+    const uint8_t *row[4];
+#pragma unroll
+    for (int rr = 0; rr < 4; ++rr)
+        row[rr] = rgb + (int64_t)(y0 + rr < H ? y0 + rr : H - 1) * stride + 3 * (int64_t)x0;
+    if (nb >= 48) {
+#pragma unroll
+        for (int rr = 0; rr < 4; ++rr)
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+                const U32x4u v = ((const U32x4u *)row[rr])[j];
+                q[rr][4 * j] = v.x;
+                q[rr][4 * j + 1] = v.y;
+                q[rr][4 * j + 2] = v.z;
+                q[rr][4 * j + 3] = v.w;
+            }
+    } else {
+        // 3 or more bytes are left.  Where only 3 are, the byte before them
+        // belongs to the row too, unless the row is a single pixel.
+#pragma unroll
+        for (int rr = 0; rr < 4; ++rr)
+#pragma unroll
+            for (int k = 0; k < 12; ++k) {
+                uint32_t v = 0;
+                if (W > 1)
+                    v = *(const U32u *)(row[rr] + (4 * k < nb - 4 ? 4 * k : nb - 4));
+                else if (k == 0)
+                    v = (uint32_t)row[rr][0] << 8 | (uint32_t)row[rr][1] << 16 | (uint32_t)row[rr][2] << 24;
+                q[rr][k] = v;
+            }
+    }
+}
+
+// Moves the dword of a partial lane that load_rgb16 took from before its place
+// (nb bytes of the row left, fewer than 48).
+__device__ __forceinline__ void fill_rgb16(int nb, uint32_t (&q)[4][12])
 {
 #pragma unroll
-    for (int rr = 0; rr < 4; ++rr) {
-        if (y0 + rr < H) {
-            const uint4 *p = (const uint4 *)(rgb + (int64_t)(y0 + rr) * stride + 3 * (int64_t)x0);
-            q[rr][0] = p[0];
-            q[rr][1] = p[1];
-            q[rr][2] = p[2];
-        } else {
-            q[rr][0] = q[rr][1] = q[rr][2] = make_uint4(0u, 0u, 0u, 0u);
-        }
+    for (int k = 0; k < 12; ++k) {
+        const int over = 4 * k + 4 - nb;  // bytes by which dword k would leave the row
+        const int sh = over <= 0 ? 0 : (over < 4 ? 8 * over : 0);
+#pragma unroll
+        for (int rr = 0; rr < 4; ++rr)
+            q[rr][k] >>= sh;
     }
 }
 
@@ -115,12 +155,23 @@ constexpr int kDefer = 8;
 // owns rows 16w .. 16w+15; lane (bx = lane & 15, by = lane >> 4) owns the
 // 4-row x 16-column block at (X0 + 16 bx, Y0 + 16 w + 4 by).  Levels 1 and 2
 // stay inside the lane, levels 3 and 4 combine lanes of the wave with
-// shuffles, levels 5 and 6 combine the four waves through LDS: a tile's 4 x 16
+// lane swaps, levels 5 and 6 combine the four waves through LDS: a tile's 4 x 16
 // level-4 pixels are parked in a ring of kDefer tiles, and a full ring is
 // turned into levels 5 and 6 by all 256 threads at once.  Each lane
 // reads 4 x 48 bytes of RGB per tile (a row of 16 lanes covers 768
-// contiguous bytes), and with 16-byte aligned rows the next tile's RGB is
-// loaded while the current one is processed.
+// contiguous bytes), and the next tile's RGB is loaded while the current one
+// is processed, whatever the rows' alignment.
+//
+// Bound by the HBM stream on large launch sets (7 x 6000x4000: 145-149 us for
+// 686 MB), by latency on small ones (one 1920x1080 image 12.2 us).  One load
+// path serves every alignment, with the loads of the next tile in flight:
+// rows at odd addresses cost no more than the cache lines they straddle.
+// Against separate, unprefetched dword and byte paths for rows that are not
+// 16-byte aligned: 7 x 3001x1999 packed rows 83.9 -> 47.0 us, eight
+// 3000x2000 quadrant views 78.2 -> 48.7 us, 9 x 8485x5657 views 523 -> 432 us.
+// Positions carried from tile to tile instead of divided out, and lane swaps
+// instead of LDS permutes (which wait for the histogram atomics queued before
+// them): 512x384 pair 10.4 -> 9.5 us, 4096x3072 pair 31.8 -> 30.1 us.
 __global__ __launch_bounds__(256) void k_pyramid(PyramidArgs a)
 {
     __shared__ uint32_t hist0[4 * kH0Copies * kHStride];  // level 0, per wave and lane group
@@ -146,8 +197,9 @@ __global__ __launch_bounds__(256) void k_pyramid(PyramidArgs a)
         (&histc[0][0])[i] = 0u;
     __syncthreads();
 
-    const int64_t per_image = (int64_t)a.tiles_x * a.tiles_y;
-    const int64_t total = per_image * a.n;
+    // Tile counts fit 32 bits (width * height < 2^31 and 16384 pixels a tile).
+    const int per_image = a.tiles_x * a.tiles_y;
+    const int total = per_image * a.n;
     // XCD-aware schedule.  Workgroups are dealt to the XCDs in turn, so
     // workgroup b runs on XCD b % kXcds, and each XCD takes a contiguous share
     // of the tiles (image-major, then row bands, then columns).  Its slots walk
@@ -155,18 +207,34 @@ __global__ __launch_bounds__(256) void k_pyramid(PyramidArgs a)
     // tiles of a row band are read at the same time on the same XCD, so the
     // cache line two of them share is fetched from HBM once.
     const int slot = blockIdx.x / kXcds, slots = gridDim.x / kXcds;
-    const int64_t xb = (int64_t)(blockIdx.x % kXcds) * a.xcd_tiles;
-    const int64_t t0 = xb + ((int64_t)slot << a.group_log2);
-    const int64_t t1 = xb + a.xcd_tiles < total ? xb + a.xcd_tiles : total;
+    const int xb = (int)(blockIdx.x % kXcds) * a.xcd_tiles;
+    const int t0 = xb + (slot << a.group_log2);
+    const int t1 = xb + a.xcd_tiles < total ? xb + a.xcd_tiles : total;
     // The share is walked in groups of 2^group_log2 consecutive tiles (one
     // launch-shape knob): slot s takes groups s, s + slots, ..., each group's
-    // tiles one after another.
-    const int64_t gmask = ((int64_t)1 << a.group_log2) - 1;
-    auto next_tile = [&](int64_t t) -> int64_t {
-        const int64_t r = t - xb;
-        if ((r & gmask) != gmask)
-            return t + 1;
-        return xb + (((r >> a.group_log2) + slots) << a.group_log2);
+    // tiles one after another.  The position (image, row band, column) is
+    // carried along: a division per tile, in the loop's serial part, would
+    // cost more than a level.
+    const int gmask = (1 << a.group_log2) - 1;
+    const int jump = ((slots - 1) << a.group_log2) + 1;  // from a group's last tile to the next group's first
+    const int jump_img = jump / per_image, jump_ty = jump % per_image / a.tiles_x, jump_tx = jump % a.tiles_x;
+    struct TilePos {
+        int t, img, ty, tx;
+    };
+    auto advance = [&](TilePos &p) {
+        const bool inside = ((p.t - xb) & gmask) != gmask;
+        p.t += inside ? 1 : jump;
+        p.tx += inside ? 1 : jump_tx;
+        p.ty += inside ? 0 : jump_ty;
+        p.img += inside ? 0 : jump_img;
+        if (p.tx >= a.tiles_x) {
+            p.tx -= a.tiles_x;
+            ++p.ty;
+        }
+        if (p.ty >= a.tiles_y) {
+            p.ty -= a.tiles_y;
+            ++p.img;
+        }
     };
 
     // Levels 5 and 6 of the `count` tiles parked in ring `bank` (image img).
@@ -211,9 +279,9 @@ __global__ __launch_bounds__(256) void k_pyramid(PyramidArgs a)
     int bank = 0, parked = 0;
 
     // Tiles of image img in XCD x's share of the tiles.
-    auto xcd_tiles_of = [&](int x, int img) -> int64_t {
-        const int64_t ib = (int64_t)img * per_image, ie = ib + per_image;
-        int64_t b = (int64_t)x * a.xcd_tiles, e = b + a.xcd_tiles < total ? b + a.xcd_tiles : total;
+    auto xcd_tiles_of = [&](int x, int img) -> int {
+        const int ib = img * per_image, ie = ib + per_image;
+        int b = x * a.xcd_tiles, e = b + a.xcd_tiles < total ? b + a.xcd_tiles : total;
         b = b > ib ? b : ib;
         e = e < ie ? e : ie;
         return e > b ? e - b : 0;
@@ -267,7 +335,7 @@ __global__ __launch_bounds__(256) void k_pyramid(PyramidArgs a)
         if (tid == 0) {
             uint32_t *tickets = merge + kXcds * kFused * 256;
             s_merge = 0;
-            if ((int64_t)atomicAdd(tickets + xcd, (uint32_t)tiles) + tiles == xcd_tiles_of(xcd, img)) {
+            if ((int)atomicAdd(tickets + xcd, (uint32_t)tiles) + tiles == xcd_tiles_of(xcd, img)) {
                 uint32_t holders = 0;
                 for (int x = 0; x < kXcds; ++x)
                     holders += xcd_tiles_of(x, img) > 0;
@@ -287,28 +355,18 @@ __global__ __launch_bounds__(256) void k_pyramid(PyramidArgs a)
         __syncthreads();
     };
 
-    // Tile t -> image and level-0 origin of this lane's block.
-    auto locate = [&](int64_t t, int &img, int &X0, int &Y0) {
-        img = (int)(t / per_image);
-        const int64_t r = t - (int64_t)img * per_image;
-        X0 = (int)(r % a.tiles_x) * kTileW;
-        Y0 = (int)(r / a.tiles_x) * kTileH;
+    auto load_tile = [&](const TilePos &p, uint32_t (&v)[4][12]) {
+        load_rgb16(a.rgb[p.img], a.stride, p.tx * kTileW + 16 * bx, p.ty * kTileH + 16 * wave + 4 * by, g.W, g.H, v);
     };
-
-    const bool fast16 = a.align == 16;
-    uint4 q[4][3];
-    if (fast16 && t0 < t1) {
-        int img, X0, Y0;
-        locate(t0, img, X0, Y0);
-        const int x0 = X0 + 16 * bx;
-        if (x0 + 15 < g.W)
-            load_rgb16(a.rgb[img], a.stride, x0, Y0 + 16 * wave + 4 * by, g.H, q);
-    }
+    uint32_t q[4][12] = {};
+    TilePos pos = {t0, t0 / per_image, t0 % per_image / a.tiles_x, t0 % per_image % a.tiles_x};
+    if (t0 < t1)
+        load_tile(pos, q);
 
     int cur = -1, cur_tiles = 0;
-    for (int64_t t = t0; t < t1; t = next_tile(t)) {
-        int img, X0, Y0;
-        locate(t, img, X0, Y0);
+    while (pos.t < t1) {
+        const int img = pos.img, X0 = pos.tx * kTileW, Y0 = pos.ty * kTileH;
+        advance(pos);
         if (img != cur) {
             if (cur >= 0)
                 flush(cur, cur_tiles);
@@ -317,81 +375,21 @@ __global__ __launch_bounds__(256) void k_pyramid(PyramidArgs a)
         }
         ++cur_tiles;
         const int x0 = X0 + 16 * bx, y0 = Y0 + 16 * wave + 4 * by;
-        const uint8_t *rgb = a.rgb[img];
         uint8_t *pyr = a.pyr[img];
         const bool full = x0 + 15 < g.W;
 
-        // ---- level 0: gray of the 4x16 block
+        // ---- level 0: gray of the 4x16 block (undefined past the image's edges)
+        if (!full)
+            fill_rgb16(3 * (g.W - x0), q);
         uint32_t gv[4][16];
-        if (fast16 && full) {
 #pragma unroll
-            for (int rr = 0; rr < 4; ++rr) {
-                const uint32_t d[12] = {q[rr][0].x, q[rr][0].y, q[rr][0].z, q[rr][0].w,
-                                        q[rr][1].x, q[rr][1].y, q[rr][1].z, q[rr][1].w,
-                                        q[rr][2].x, q[rr][2].y, q[rr][2].z, q[rr][2].w};
+        for (int rr = 0; rr < 4; ++rr)
 #pragma unroll
-                for (int k = 0; k < 4; ++k)
-                    gray4(d[3 * k], d[3 * k + 1], d[3 * k + 2], &gv[rr][4 * k]);
-            }
-        } else if (a.align >= 4 && full) {
-            uint32_t d[4][12];
-#pragma unroll
-            for (int rr = 0; rr < 4; ++rr) {
-                const uint32_t *p = (const uint32_t *)(rgb + (int64_t)(y0 + rr) * a.stride + 3 * (int64_t)x0);
-#pragma unroll
-                for (int k = 0; k < 12; ++k)
-                    d[rr][k] = (y0 + rr < g.H) ? p[k] : 0u;
-            }
-#pragma unroll
-            for (int rr = 0; rr < 4; ++rr)
-#pragma unroll
-                for (int k = 0; k < 4; ++k)
-                    gray4(d[rr][3 * k], d[rr][3 * k + 1], d[rr][3 * k + 2], &gv[rr][4 * k]);
-        } else if (full) {
-            // Rows at any byte alignment: the whole dwords overlapping the lane's
-            // 48 bytes (12, or 13 when the start is not 4-aligned; each holds a
-            // byte of the segment, so none reaches into a page the row does not
-            // touch), moved into place with v_alignbyte_b32.
-            uint32_t d[4][12];
-#pragma unroll
-            for (int rr = 0; rr < 4; ++rr) {
-                const uint8_t *row = rgb + (int64_t)(y0 + rr) * a.stride + 3 * (int64_t)x0;
-                const uint32_t sh = (uint32_t)(uintptr_t)row & 3u;
-                const uint32_t *p = (const uint32_t *)((uintptr_t)row - sh);
-                uint32_t w[13];
-                const bool in = y0 + rr < g.H;
-#pragma unroll
-                for (int k = 0; k < 12; ++k)
-                    w[k] = in ? p[k] : 0u;
-                w[12] = in && sh ? p[12] : 0u;
-#pragma unroll
-                for (int k = 0; k < 12; ++k)
-                    d[rr][k] = __builtin_amdgcn_alignbyte(w[k + 1], w[k], sh);
-            }
-#pragma unroll
-            for (int rr = 0; rr < 4; ++rr)
-#pragma unroll
-                for (int k = 0; k < 4; ++k)
-                    gray4(d[rr][3 * k], d[rr][3 * k + 1], d[rr][3 * k + 2], &gv[rr][4 * k]);
-        } else {
-#pragma unroll
-            for (int rr = 0; rr < 4; ++rr) {
-                const uint8_t *row = rgb + (int64_t)(y0 + rr) * a.stride + 3 * (int64_t)x0;
-#pragma unroll
-                for (int c = 0; c < 16; ++c)
-                    gv[rr][c] = (y0 + rr < g.H && x0 + c < g.W)
-                                    ? gray3(row[3 * c], row[3 * c + 1], row[3 * c + 2])
-                                    : 0u;
-            }
-        }
+            for (int k = 0; k < 4; ++k)
+                gray4(q[rr][3 * k], q[rr][3 * k + 1], q[rr][3 * k + 2], &gv[rr][4 * k]);
         // ---- prefetch the next tile's RGB while this one is processed
-        if (fast16 && next_tile(t) < t1) {
-            int img2, X2, Y2;
-            locate(next_tile(t), img2, X2, Y2);
-            const int x2 = X2 + 16 * bx;
-            if (x2 + 15 < g.W)
-                load_rgb16(a.rgb[img2], a.stride, x2, Y2 + 16 * wave + 4 * by, g.H, q);
-        }
+        if (pos.t < t1)
+            load_tile(pos, q);
         {
             const LevelGeom &lv = g.lv[0];
 #pragma unroll
@@ -437,10 +435,16 @@ __global__ __launch_bounds__(256) void k_pyramid(PyramidArgs a)
                     if (!a.skip_l1)
                         *(uint2 *)(pyr + l1.gray_off + (int64_t)(y1 + i) * l1.gray_pitch + x1) =
                             make_uint2(pack4(&u1[i][0]), pack4(&u1[i][4]));
+                    if (x1 + 7 < l1.w) {
 #pragma unroll
-                    for (int j = 0; j < 8; ++j)
-                        if (x1 + j < l1.w)
+                        for (int j = 0; j < 8; ++j)
                             atomicAdd(&hist1[wave][u1[i][j]], 1u);
+                    } else {
+#pragma unroll
+                        for (int j = 0; j < 8; ++j)
+                            if (x1 + j < l1.w)
+                                atomicAdd(&hist1[wave][u1[i][j]], 1u);
+                    }
                 }
             }
             if (fused > 2) {
@@ -459,28 +463,23 @@ __global__ __launch_bounds__(256) void k_pyramid(PyramidArgs a)
                             atomicAdd(&histc[0][u2[j]], 1u);
                 }
                 if (fused > 3) {
-                    // ---- level 3: columns inside the lane, rows from lane ^ 16 (by ^ 1)
-                    uint32_t u3[2];
-#pragma unroll
-                    for (int j = 0; j < 2; ++j) {
-                        uint32_t s3 = u2[2 * j] + u2[2 * j + 1];
-                        s3 += __shfl_xor(s3, 16);
-                        u3[j] = s3 >> 2;
-                    }
+                    // ---- level 3: columns inside the lane, rows from lane ^ 16 (by ^ 1).
+                    // The exchange is a VALU one (no LDS: a ds_bpermute would wait for
+                    // every histogram atomic before it) and leaves column by & 1 of the
+                    // lane's two in lane (bx, by).
+                    const U32x2 r3 = __builtin_amdgcn_permlane16_swap(u2[0] + u2[1], u2[2] + u2[3], false, false);
+                    const uint32_t u3 = (r3.x + r3.y) >> 2;
                     const LevelGeom &l3 = g.lv[3];
-                    const int x3 = x0 >> 3, y3 = y0 >> 3;
-                    if ((by & 1) == 0 && y3 < l3.h && x3 < l3.w) {
-                        *(uint16_t *)(pyr + l3.gray_off + (int64_t)y3 * l3.gray_pitch + x3) =
-                            (uint16_t)(u3[0] | (u3[1] << 8));
-                        atomicAdd(&histc[1][u3[0]], 1u);
-                        if (x3 + 1 < l3.w)
-                            atomicAdd(&histc[1][u3[1]], 1u);
+                    const int x3 = (x0 >> 3) + (by & 1), y3 = y0 >> 3;
+                    if (y3 < l3.h && x3 < l3.w) {
+                        pyr[l3.gray_off + (int64_t)y3 * l3.gray_pitch + x3] = (uint8_t)u3;
+                        atomicAdd(&histc[1][u3], 1u);
                     }
                     if (fused > 4) {
-                        // ---- level 4: rows from lane ^ 32 (by ^ 2); owners are lanes 0..15
-                        uint32_t s4 = u3[0] + u3[1];
-                        s4 += __shfl_xor(s4, 32);
-                        const uint32_t u4 = s4 >> 2;
+                        // ---- level 4: the four lanes (bx, 0..3); owners are lanes 0..15
+                        const U32x2 c4 = __builtin_amdgcn_permlane16_swap(u3, u3, false, false);
+                        const U32x2 r4 = __builtin_amdgcn_permlane32_swap(c4.x + c4.y, c4.x + c4.y, false, false);
+                        const uint32_t u4 = (r4.x + r4.y) >> 2;
                         const LevelGeom &l4 = g.lv[4];
                         const int x4 = x0 >> 4, y4 = y0 >> 4;
                         if (by == 0 && y4 < l4.h && x4 < l4.w) {

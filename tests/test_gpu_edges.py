@@ -1,0 +1,63 @@
+"""Edges of the kernels' tiles, lanes and dispatch rules against the oracle, bit for bit.
+
+Everything compared is a whole number or a byte, so the tolerance is zero.
+"""
+
+import numpy as np
+import pytest
+
+import oracle
+from mtb_decode import bitmaps, gray_levels, histograms, medians
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+DEV = "cuda:0"
+
+
+@pytest.fixture(scope="module")
+def mtb():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2007_06483_amd as m
+
+    m.lib()
+    return m
+
+
+def _view(img, extra, offset):
+    """Device view of img whose rows are 3W + extra bytes apart, starting offset bytes in."""
+    h, w, _ = img.shape
+    stride = 3 * w + extra
+    buf = np.full(offset + stride * h, 201, np.uint8)
+    rows = buf[offset:].reshape(h, stride)
+    rows[:, :3 * w] = img.reshape(h, 3 * w)
+    return torch.as_strided(torch.from_numpy(buf).to(DEV), (h, w, 3), (stride, 3, 1), offset)
+
+
+def _check_pyramid(mtb, d_img, img, L):
+    h, w, _ = img.shape
+    lay = mtb.mtb_get_layout(w, h, L)
+    pyr = mtb.mtb_build_pyramid(d_img, L)
+    bm = mtb.mtb_bitmaps(pyr, w, h, L)
+    torch.cuda.synchronize()
+    pyr_h, bm_h = pyr.cpu().numpy(), bm.cpu().numpy()
+    want = oracle.pyramid(img, L)
+    for l, g in enumerate(gray_levels(pyr_h, lay)):
+        assert np.array_equal(g, want.gray(l)), f"gray level {l}"
+    assert np.array_equal(histograms(pyr_h, lay), want.hist)
+    assert np.array_equal(medians(bm_h, lay), want.median)
+    for l, (t, e, tp, ep) in enumerate(bitmaps(bm_h, lay)):
+        assert np.array_equal(t, want.tb(l)) and np.array_equal(e, want.eb(l)), f"bitmaps level {l}"
+        assert not tp.any() and not ep.any(), f"padding bits set at level {l}"
+
+
+# A lane takes 16 pixels of a row: widths around its multiples, and the widths
+# at which the last lane holds 1, 2 or 3 pixels (3 to 9 bytes).
+@pytest.mark.parametrize("w", [1, 2, 3, 4, 5, 15, 16, 17, 18, 21, 31, 33, 255, 257, 262, 271])
+@pytest.mark.parametrize("extra,offset", [(0, 0), (1, 0), (0, 1), (3, 2), (16, 15)])
+def test_pyramid_row_ends_at_every_alignment(mtb, w, extra, offset):
+    img = np.random.default_rng(1000 * w + 10 * extra + offset).integers(0, 256, (67, w, 3), dtype=np.uint8)
+    L = min(7, mtb.mtb_max_levels(w, 67))
+    _check_pyramid(mtb, _view(img, extra, offset), img, L)
