@@ -1396,13 +1396,11 @@ mtb_status mtb_apply_shifts(const uint8_t *const *h_d_rgb, int32_t n, int32_t wi
         return MTB_ERR_INVALID_ARG;
     ApplyArgs a;
     memset(&a, 0, sizeof(a));
-    bool aligned = row_stride % 4 == 0 && out_stride % 16 == 0;
     for (int i = 0; i < n; ++i) {
         if (!h_d_rgb[i] || !h_d_out[i])
             return MTB_ERR_INVALID_ARG;
         a.rgb[i] = h_d_rgb[i];
         a.out[i] = h_d_out[i];
-        aligned = aligned && (uintptr_t)h_d_rgb[i] % 4 == 0 && (uintptr_t)h_d_out[i] % 16 == 0;
     }
     const int cus = current_device_cus();
     if (cus <= 0)
@@ -1414,7 +1412,6 @@ mtb_status mtb_apply_shifts(const uint8_t *const *h_d_rgb, int32_t n, int32_t wi
     a.width = width;
     a.height = height;
     a.fill = fill;
-    a.aligned = aligned ? 1 : 0;
     return device_status(launch_apply(a, cus, (hipStream_t)stream));
 }
 

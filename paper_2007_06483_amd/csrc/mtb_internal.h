@@ -169,8 +169,7 @@ struct ApplyArgs {
     int64_t stride, out_stride;
     int32_t n, width, height;
     int32_t fill;           // 0: zeros outside the image, 1: nearest edge pixel
-    int32_t aligned;        // input rows 4-byte aligned and output rows 16-byte aligned
-    int32_t pad_;
+    int64_t runs;           // work items of a row (set by launch_apply)
 };
 
 struct ZeroArgs {

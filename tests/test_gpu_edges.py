@@ -61,3 +61,27 @@ def test_pyramid_row_ends_at_every_alignment(mtb, w, extra, offset):
     img = np.random.default_rng(1000 * w + 10 * extra + offset).integers(0, 256, (67, w, 3), dtype=np.uint8)
     L = min(7, mtb.mtb_max_levels(w, 67))
     _check_pyramid(mtb, _view(img, extra, offset), img, L)
+
+
+# k_apply writes 16-byte chunks at aligned output addresses in runs of whole
+# wavefronts: rows around a chunk (5, 6 pixels), around 1, 4 and 5 KiB, and
+# shifts that leave no, some and every source column inside, with input and
+# output rows at every kind of alignment.
+@pytest.mark.parametrize("w", [1, 5, 6, 11, 341, 342, 1365, 1706, 1707, 1712])
+@pytest.mark.parametrize("extra,offset,out_extra,out_offset", [(0, 0, 0, 0), (1, 3, 0, 5), (4, 4, 7, 0), (16, 1, 13, 2)])
+def test_apply_rows_at_every_alignment(mtb, w, extra, offset, out_extra, out_offset):
+    h = 9
+    rng = np.random.default_rng(w * 100 + extra)
+    imgs = [rng.integers(0, 256, (h, w, 3), dtype=np.uint8) for _ in range(6)]
+    shifts = [(0, 0), (1, -1), (-w, 0), (w - 1, 8), (-5, -9), (2, 2)]
+    sh = torch.tensor(shifts, dtype=torch.int32, device=DEV)
+    for fill in (mtb.MTB_FILL_ZERO, mtb.MTB_FILL_EDGE):
+        d = [_view(im, extra, offset) for im in imgs]
+        outs = [_view(np.zeros_like(im), out_extra, out_offset) for im in imgs]
+        mtb.mtb_apply_shifts(d, sh, fill, out=outs)
+        torch.cuda.synchronize()
+        for im, o, (dx, dy) in zip(imgs, outs, shifts):
+            assert np.array_equal(o.cpu().numpy(), oracle.apply_shift(im, dx, dy, fill)), (fill, dx, dy)
+            if out_extra:  # row padding stays as it was
+                pad = o.as_strided((h - 1, out_extra), (o.stride(0), 1), o.storage_offset() + 3 * w)
+                assert (pad == 201).all()
