@@ -72,14 +72,15 @@ __device__ __forceinline__ void store_shared(uint32_t *p, uint32_t v)
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Level-0 histogram privatisation: kH0Copies copies per wave; copies kHStride
-// (odd) words apart, so that equal values from lanes of different copies fall
-// into different LDS banks.  Atomics to one address serialise, and nearby
-// pixels are often equal, so the lanes sharing a copy should hold pixels far
-// apart: lane (bx, by) (pixels at x = 16 bx + c, y = 4 by + r) adds into copy
-// (bx + 2 by) mod 8, whose lanes are at least 32 columns or 8 rows apart.
-constexpr int kH0Copies = 8;
-constexpr int kHStride = 257;
+// Histogram privatisation in k_pyramid.  LDS atomics of one instruction to one
+// address are made one after another, and flat parts of an image (the dark
+// and the saturated ones above all) put a whole wavefront into one bin, so a
+// level's histogram has a column of counters per group of lanes: bin v of
+// column c at word kCols v + c, which puts lanes of different columns into
+// different banks too, whatever their bins.  Columns are given by the work:
+// 16 for levels 0 and 1 (64 and 16 adds a tile and lane), 8 for level 2 (4),
+// one for levels 3 to 6 (1 or less).
+constexpr int kCols01 = 16, kCols2 = 8;
 
 // Clang vector type, the operand type the nontemporal builtins accept.
 typedef uint32_t U32x4 __attribute__((ext_vector_type(4)));
@@ -162,24 +163,30 @@ constexpr int kDefer = 8;
 // contiguous bytes), and the next tile's RGB is loaded while the current one
 // is processed, whatever the rows' alignment.
 //
-// Bound by the HBM stream on large launch sets (7 x 6000x4000: 145-149 us for
-// 686 MB), by latency on small ones (one 1920x1080 image 12.2 us).  One load
-// path serves every alignment, with the loads of the next tile in flight:
-// rows at odd addresses cost no more than the cache lines they straddle.
-// Against separate, unprefetched dword and byte paths for rows that are not
-// 16-byte aligned: 7 x 3001x1999 packed rows 83.9 -> 47.0 us, eight
-// 3000x2000 quadrant views 78.2 -> 48.7 us, 9 x 8485x5657 views 523 -> 432 us.
-// Positions carried from tile to tile instead of divided out, and lane swaps
-// instead of LDS permutes (which wait for the histogram atomics queued before
-// them): 512x384 pair 10.4 -> 9.5 us, 4096x3072 pair 31.8 -> 30.1 us.
-__global__ __launch_bounds__(256) void k_pyramid(PyramidArgs a)
+// Bound by the HBM stream on large launch sets (7 x 6000x4000: 138 us for 686
+// MB, 0.92 of the rate a plain kernel streams the same mix of reads and writes
+// at), by latency on small ones (one 1920x1080 image 12 us).  What it took:
+//  - One load path for every alignment, with the loads of the next tile in
+//    flight: rows at odd addresses cost no more than the cache lines they
+//    straddle.  Against separate, unprefetched dword and byte paths: 7 x
+//    3001x1999 packed rows 83.9 -> 47.0 us, eight 3000x2000 quadrant views
+//    78.2 -> 48.7 us, 9 x 8485x5657 views 523 -> 432 us.
+//  - Lane swaps instead of LDS permutes, which wait for the histogram atomics
+//    queued before them: 512x384 pair 10.4 -> 9.5 us.
+//  - Histogram columns per group of lanes: 7 x 6000x4000 images of one value
+//    277 -> 139 us, as fast as noise (135; it was 145); before, the time
+//    depended on the content.
+//  - Claimed tiles instead of equal shares: 7 x 6000x4000 144 -> 137 us.
+// Three wavefronts a SIMD (the registers allow 168 each): the compiler's own
+// choice of 181 would leave two.
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_pyramid(PyramidArgs a)
 {
-    __shared__ uint32_t hist0[4 * kH0Copies * kHStride];  // level 0, per wave and lane group
-    __shared__ uint32_t hist1[4][256];                    // level 1, per wave
-    __shared__ uint32_t histc[kFused - 2][256];           // levels 2 .. 6, whole workgroup
+    constexpr int kHWords = 256 * (2 * kCols01 + kCols2 + kFused - 3);
+    __shared__ __attribute__((aligned(16))) uint32_t hist[kHWords];  // levels 0, 1 and 2, then 3 .. 6
     __shared__ uint32_t lvl4[2][kDefer][4][16];           // level-4 pixels of deferred tiles, two rings
     __shared__ int2 ring_pos[2][kDefer];                  // level-0 origin of each deferred tile
     __shared__ int s_merge;                               // this workgroup merges the image's copies
+    __shared__ int4 s_next[2];                            // the tile after next: image (-1: none), column, row band
 
     const int tid = threadIdx.x;
     const int wave = wave_id();
@@ -187,54 +194,46 @@ __global__ __launch_bounds__(256) void k_pyramid(PyramidArgs a)
     const int bx = lane & 15, by = lane >> 4;
     const Geometry &g = a.g;
     const int fused = g.L < kFused ? g.L : kFused;
-    uint32_t *h0 = hist0 + (wave * kH0Copies + ((bx + 2 * by) & (kH0Copies - 1))) * kHStride;
-
-    for (int i = tid; i < 4 * kH0Copies * kHStride; i += 256)
-        hist0[i] = 0u;
-    for (int i = tid; i < 4 * 256; i += 256)
-        (&hist1[0][0])[i] = 0u;
-    for (int i = tid; i < (kFused - 2) * 256; i += 256)
-        (&histc[0][0])[i] = 0u;
-    __syncthreads();
+    uint32_t *h0 = hist + (lane & (kCols01 - 1)), *h1 = h0 + 256 * kCols01;
+    uint32_t *h2 = hist + 256 * 2 * kCols01 + (lane & (kCols2 - 1));
+    uint32_t *hc = hist + 256 * (2 * kCols01 + kCols2);  // level l at hc + 256 (l - 3)
 
     // Tile counts fit 32 bits (width * height < 2^31 and 16384 pixels a tile).
     const int per_image = a.tiles_x * a.tiles_y;
     const int total = per_image * a.n;
     // XCD-aware schedule.  Workgroups are dealt to the XCDs in turn, so
     // workgroup b runs on XCD b % kXcds, and each XCD takes a contiguous share
-    // of the tiles (image-major, then row bands, then columns).  Its slots walk
-    // that share in step, slot s taking tiles s, s + slots, ...: neighbouring
-    // tiles of a row band are read at the same time on the same XCD, so the
-    // cache line two of them share is fetched from HBM once.
-    const int slot = blockIdx.x / kXcds, slots = gridDim.x / kXcds;
-    const int xb = (int)(blockIdx.x % kXcds) * a.xcd_tiles;
+    // of the tiles (image-major, then row bands, then columns).  Its workgroups
+    // walk that share together: neighbouring tiles of a row band are read at
+    // about the same time on the same XCD, so the cache line two of them share
+    // is fetched from HBM once.  A workgroup's first two tiles are its slot's (slot and
+    // slot + slots); every further one it claims from its XCD's counter, because the workgroups of a
+    // compute unit do not progress alike (with equal, fixed shares of 7 x
+    // 6000x4000 they ended between 90 and 148 us after the start).  Only speed
+    // depends on which workgroup gets a tile.
+    const int xcd = blockIdx.x % kXcds, slot = blockIdx.x / kXcds, slots = gridDim.x / kXcds;
+    const int xb = xcd * a.xcd_tiles;
     const int t0 = xb + (slot << a.group_log2);
     const int t1 = xb + a.xcd_tiles < total ? xb + a.xcd_tiles : total;
-    // The share is walked in groups of 2^group_log2 consecutive tiles (one
-    // launch-shape knob): slot s takes groups s, s + slots, ..., each group's
-    // tiles one after another.  The position (image, row band, column) is
-    // carried along: a division per tile, in the loop's serial part, would
-    // cost more than a level.
+    if (t0 >= t1)
+        return;
+    // The claims are made in groups of 2^group_log2 consecutive tiles (one
+    // launch-shape knob), by thread 0; each claim's counter value is asked for
+    // a tile before it is needed, and the first one not before the second tile,
+    // so that a launch's start does not wait for the counters.
+    uint32_t *claims = (uint32_t *)(a.pyr[xcd % a.n] + g.hmerge_off) + kXcds * kFused * 256 + 32 + xcd / a.n;
+    const bool claiming = a.xcd_tiles > (2 * slots << a.group_log2);
     const int gmask = (1 << a.group_log2) - 1;
-    const int jump = ((slots - 1) << a.group_log2) + 1;  // from a group's last tile to the next group's first
-    const int jump_img = jump / per_image, jump_ty = jump % per_image / a.tiles_x, jump_tx = jump % a.tiles_x;
-    struct TilePos {
-        int t, img, ty, tx;
-    };
-    auto advance = [&](TilePos &p) {
-        const bool inside = ((p.t - xb) & gmask) != gmask;
-        p.t += inside ? 1 : jump;
-        p.tx += inside ? 1 : jump_tx;
-        p.ty += inside ? 0 : jump_ty;
-        p.img += inside ? 0 : jump_img;
-        if (p.tx >= a.tiles_x) {
-            p.tx -= a.tiles_x;
-            ++p.ty;
+    int gen_t = t0;        // thread 0: the last tile published
+    uint32_t claimed = slot;  // thread 0: the next group to publish, less slots
+    auto publish = [&](int4 *next) {
+        ++gen_t;
+        if (((gen_t - xb) & gmask) == 0) {
+            gen_t = xb + (int)((slots + claimed) << a.group_log2);
+            claimed = claiming ? slots + atomicAdd(claims, 1u) : 1u << 24;
         }
-        if (p.ty >= a.tiles_y) {
-            p.ty -= a.tiles_y;
-            ++p.img;
-        }
+        const int r = gen_t % per_image;
+        *next = gen_t < t1 ? make_int4(gen_t / per_image, r % a.tiles_x, r / a.tiles_x, 0) : make_int4(-1, 0, 0, 0);
     };
 
     // Levels 5 and 6 of the `count` tiles parked in ring `bank` (image img).
@@ -256,7 +255,7 @@ __global__ __launch_bounds__(256) void k_pyramid(PyramidArgs a)
             const int x5 = (o.x >> 5) + j5, y5 = (o.y >> 5) + i5;
             if (y5 < l5.h && x5 < l5.w) {
                 pyr[l5.gray_off + (int64_t)y5 * l5.gray_pitch + x5] = (uint8_t)u5;
-                atomicAdd(&histc[3][u5], 1u);
+                atomicAdd(hc + 2 * 256 + u5, 1u);
             }
         } else if (fused > 6) {
             const int j6 = r - 16;
@@ -272,7 +271,7 @@ __global__ __launch_bounds__(256) void k_pyramid(PyramidArgs a)
             const int x6 = (o.x >> 6) + j6, y6 = o.y >> 6;
             if (y6 < l6.h && x6 < l6.w) {
                 pyr[l6.gray_off + (int64_t)y6 * l6.gray_pitch + x6] = (uint8_t)u6;
-                atomicAdd(&histc[4][u6], 1u);
+                atomicAdd(hc + 3 * 256 + u6, 1u);
             }
         }
     };
@@ -306,22 +305,24 @@ __global__ __launch_bounds__(256) void k_pyramid(PyramidArgs a)
             parked = 0;
             __syncthreads();
         }
-        const int xcd = blockIdx.x % kXcds;
         uint32_t *merge = (uint32_t *)(a.pyr[img] + g.hmerge_off);
         uint32_t *gh = a.merge ? merge + xcd * kFused * 256 : (uint32_t *)(a.pyr[img] + g.hist_off);
+#pragma unroll 1
         for (int l = 0; l < fused; ++l) {
+            // The columns of bin tid, cleared for the next image.
             uint32_t s = 0;
-            if (l == 0) {
-                for (int c = 0; c < 4 * kH0Copies; ++c) {
-                    s += hist0[c * kHStride + tid];
-                    hist0[c * kHStride + tid] = 0u;
+            if (l < 3) {
+                uint4 *h = (uint4 *)(hist + (l < 2 ? 256 * kCols01 * l + kCols01 * tid : 256 * 2 * kCols01 + kCols2 * tid));
+                const int words = l < 2 ? kCols01 / 4 : kCols2 / 4;
+#pragma unroll 1
+                for (int c = 0; c < words; ++c) {
+                    const uint4 v = h[c];
+                    s += v.x + v.y + v.z + v.w;
+                    h[c] = make_uint4(0u, 0u, 0u, 0u);
                 }
-            } else if (l == 1) {
-                s = hist1[0][tid] + hist1[1][tid] + hist1[2][tid] + hist1[3][tid];
-                hist1[0][tid] = hist1[1][tid] = hist1[2][tid] = hist1[3][tid] = 0u;
             } else {
-                s = histc[l - 2][tid];
-                histc[l - 2][tid] = 0u;
+                s = hc[256 * (l - 3) + tid];
+                hc[256 * (l - 3) + tid] = 0u;
             }
             if (s)
                 atomicAdd(gh + l * 256 + tid, s);
@@ -355,18 +356,25 @@ __global__ __launch_bounds__(256) void k_pyramid(PyramidArgs a)
         __syncthreads();
     };
 
-    auto load_tile = [&](const TilePos &p, uint32_t (&v)[4][12]) {
-        load_rgb16(a.rgb[p.img], a.stride, p.tx * kTileW + 16 * bx, p.ty * kTileH + 16 * wave + 4 * by, g.W, g.H, v);
+    auto load_tile = [&](int img, int tx, int ty, uint32_t (&v)[4][12]) {
+        load_rgb16(a.rgb[img], a.stride, tx * kTileW + 16 * bx, ty * kTileH + 16 * wave + 4 * by, g.W, g.H, v);
     };
     uint32_t q[4][12] = {};
-    TilePos pos = {t0, t0 / per_image, t0 % per_image / a.tiles_x, t0 % per_image % a.tiles_x};
-    if (t0 < t1)
-        load_tile(pos, q);
+    int img = t0 / per_image, tx = t0 % per_image % a.tiles_x, ty = t0 % per_image / a.tiles_x;
+    load_tile(img, tx, ty, q);
+#pragma unroll 1
+    for (int i = tid; i < kHWords / 4; i += 256)
+        ((uint4 *)hist)[i] = make_uint4(0u, 0u, 0u, 0u);
+    if (tid == 0)
+        publish(&s_next[0]);
+    __syncthreads();
 
     int cur = -1, cur_tiles = 0;
-    while (pos.t < t1) {
-        const int img = pos.img, X0 = pos.tx * kTileW, Y0 = pos.ty * kTileH;
-        advance(pos);
+    for (int it = 0;; ++it) {
+        const int X0 = tx * kTileW, Y0 = ty * kTileH;
+        const int4 next = s_next[it & 1];
+        const int next_img = __builtin_amdgcn_readfirstlane(next.x), next_tx = __builtin_amdgcn_readfirstlane(next.y),
+                  next_ty = __builtin_amdgcn_readfirstlane(next.z);
         if (img != cur) {
             if (cur >= 0)
                 flush(cur, cur_tiles);
@@ -388,8 +396,14 @@ __global__ __launch_bounds__(256) void k_pyramid(PyramidArgs a)
             for (int k = 0; k < 4; ++k)
                 gray4(q[rr][3 * k], q[rr][3 * k + 1], q[rr][3 * k + 2], &gv[rr][4 * k]);
         // ---- prefetch the next tile's RGB while this one is processed
-        if (pos.t < t1)
-            load_tile(pos, q);
+        if (next_img >= 0) {
+            // Take the claim's answer before the loads are issued: waiting for it
+            // after them would wait for them too.
+            asm volatile("" : "+v"(claimed));
+            load_tile(next_img, next_tx, next_ty, q);
+            if (tid == 0)
+                publish(&s_next[(it + 1) & 1]);
+        }
         {
             const LevelGeom &lv = g.lv[0];
 #pragma unroll
@@ -408,12 +422,12 @@ __global__ __launch_bounds__(256) void k_pyramid(PyramidArgs a)
                     if (full) {
 #pragma unroll
                         for (int c = 0; c < 16; ++c)
-                            atomicAdd(&h0[gv[rr][c]], 1u);
+                            atomicAdd(h0 + kCols01 * gv[rr][c], 1u);
                     } else {
 #pragma unroll
                         for (int c = 0; c < 16; ++c)
                             if (x0 + c < g.W)
-                                atomicAdd(&h0[gv[rr][c]], 1u);
+                                atomicAdd(h0 + kCols01 * gv[rr][c], 1u);
                     }
                 }
             }
@@ -438,12 +452,12 @@ __global__ __launch_bounds__(256) void k_pyramid(PyramidArgs a)
                     if (x1 + 7 < l1.w) {
 #pragma unroll
                         for (int j = 0; j < 8; ++j)
-                            atomicAdd(&hist1[wave][u1[i][j]], 1u);
+                            atomicAdd(h1 + kCols01 * u1[i][j], 1u);
                     } else {
 #pragma unroll
                         for (int j = 0; j < 8; ++j)
                             if (x1 + j < l1.w)
-                                atomicAdd(&hist1[wave][u1[i][j]], 1u);
+                                atomicAdd(h1 + kCols01 * u1[i][j], 1u);
                     }
                 }
             }
@@ -460,7 +474,7 @@ __global__ __launch_bounds__(256) void k_pyramid(PyramidArgs a)
 #pragma unroll
                     for (int j = 0; j < 4; ++j)
                         if (x2 + j < l2.w)
-                            atomicAdd(&histc[0][u2[j]], 1u);
+                            atomicAdd(h2 + kCols2 * u2[j], 1u);
                 }
                 if (fused > 3) {
                     // ---- level 3: columns inside the lane, rows from lane ^ 16 (by ^ 1).
@@ -473,7 +487,7 @@ __global__ __launch_bounds__(256) void k_pyramid(PyramidArgs a)
                     const int x3 = (x0 >> 3) + (by & 1), y3 = y0 >> 3;
                     if (y3 < l3.h && x3 < l3.w) {
                         pyr[l3.gray_off + (int64_t)y3 * l3.gray_pitch + x3] = (uint8_t)u3;
-                        atomicAdd(&histc[1][u3], 1u);
+                        atomicAdd(hc + u3, 1u);
                     }
                     if (fused > 4) {
                         // ---- level 4: the four lanes (bx, 0..3); owners are lanes 0..15
@@ -484,29 +498,35 @@ __global__ __launch_bounds__(256) void k_pyramid(PyramidArgs a)
                         const int x4 = x0 >> 4, y4 = y0 >> 4;
                         if (by == 0 && y4 < l4.h && x4 < l4.w) {
                             pyr[l4.gray_off + (int64_t)y4 * l4.gray_pitch + x4] = (uint8_t)u4;
-                            atomicAdd(&histc[2][u4], 1u);
+                            atomicAdd(hc + 256 + u4, 1u);
                         }
                         if (fused > 5) {
                             // ---- levels 5 and 6: park the tile's 4 x 16 level-4 pixels
-                            // (row = wave, column = bx); a full ring is drained.
+                            // (row = wave, column = bx).
                             if (by == 0)
                                 lvl4[bank][parked][wave][bx] = u4;
                             if (tid == 0)
                                 ring_pos[bank][parked] = make_int2(X0, Y0);
-                            if (++parked == kDefer) {
-                                __syncthreads();
-                                drain(img, bank, kDefer);
-                                bank ^= 1;
-                                parked = 0;
-                            }
+                            ++parked;
                         }
                     }
                 }
             }
         }
+        if (next_img < 0)
+            break;
+        // Publishes the tile after next and the parked pixels; a full ring is drained.
+        __syncthreads();
+        if (parked == kDefer) {
+            drain(img, bank, kDefer);
+            bank ^= 1;
+            parked = 0;
+        }
+        img = next_img;
+        tx = next_tx;
+        ty = next_ty;
     }
-    if (cur >= 0)
-        flush(cur, cur_tiles);
+    flush(cur, cur_tiles);
 }
 
 // Levels kFused .. L-1, each the floor 2x2 mean of the level below; one

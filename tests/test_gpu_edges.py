@@ -7,7 +7,7 @@ import numpy as np
 import pytest
 
 import oracle
-from mtb_decode import bitmaps, gray_levels, histograms, medians
+from mtb_decode import bitmaps, gray_levels, histograms, medians, stack_workspace
 
 pytestmark = pytest.mark.gpu
 
@@ -85,3 +85,32 @@ def test_apply_rows_at_every_alignment(mtb, w, extra, offset, out_extra, out_off
             if out_extra:  # row padding stays as it was
                 pad = o.as_strided((h - 1, out_extra), (o.stride(0), 1), o.storage_offset() + 3 * w)
                 assert (pad == 201).all()
+
+
+# Beyond two tiles a workgroup, k_pyramid's workgroups claim tiles (in groups of
+# 1, 2 or 4 by launch shape); every tile must be counted exactly once, merged
+# histograms or not, also where every pixel falls into one bin.
+@pytest.mark.parametrize("n,w,h,pct,group", [(3, 4096, 3072, 25, 4), (3, 4096, 3072, 25, 2), (3, 4096, 3072, 25, 1),
+                                             (2, 4001, 3003, 25, 1), (1, 6000, 4200, 100, 1), (5, 3000, 2000, 50, 2)])
+def test_pyramid_claimed_tiles(mtb, n, w, h, pct, group):
+    L = 7
+    rng = np.random.default_rng(w + n)
+    imgs = [rng.integers(0, 256, (h, w, 3), dtype=np.uint8)]
+    imgs += [np.full((h, w, 3), 255, np.uint8), imgs[0] // 32, imgs[0] // 2, imgs[0]][:n - 1]
+    stride = 3 * w
+    mtb.mtb_set_shape(n, w, h, stride, L, {"pyramid_slots_pct": pct, "pyramid_tile_group": group})
+    try:
+        d = [_view(im, 0, 0) for im in imgs]
+        lay = mtb.mtb_get_layout(w, h, L)
+        for _ in range(3):  # the claims start from zero on every call
+            got = mtb.mtb_align_stack(d, L)
+            torch.cuda.synchronize()
+            pyrs, bms = stack_workspace(mtb, got["workspace"], n, lay)
+            for im, p, b in zip(imgs, pyrs, bms):
+                want = oracle.pyramid(im, L)
+                assert np.array_equal(histograms(p, lay), want.hist)
+                assert np.array_equal(medians(b, lay), want.median)
+                for l, g in enumerate(gray_levels(p, lay)):
+                    assert np.array_equal(g, want.gray(l)), f"gray level {l}"
+    finally:
+        mtb.mtb_tune_reset()
