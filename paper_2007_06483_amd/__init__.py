@@ -293,9 +293,28 @@ def _device_u8(t: torch.Tensor, what: str):
 def _rgb_geometry(img: torch.Tensor):
     """(H, W, 3) uint8 device tensor with packed pixels -> (W, H, row_stride_bytes)."""
     _device_u8(img, "image")
-    if img.dim() != 3 or img.shape[2] != 3 or img.stride(2) != 1 or img.stride(1) != 3:
+    shape, strides = img.shape, img.stride()
+    if len(shape) != 3 or shape[2] != 3 or strides[2] != 1 or strides[1] != 3:
         raise ValueError("image must be (H, W, 3) with interleaved R,G,B bytes")
-    return int(img.shape[1]), int(img.shape[0]), int(img.stride(0))
+    return shape[1], shape[0], strides[0]
+
+
+def _stack_geometry(images, message: str, same_device: bool = True):
+    """_rgb_geometry of a stack whose images must all share it (and the device).
+
+    An image of the first one's shape, strides, type and device needs no check of its
+    own: the marshalling of a call with many images is bound by these look-ups.
+    """
+    first = images[0]
+    geo = _rgb_geometry(first)
+    shape, strides, dev = first.shape, first.stride(), first.device
+    for im in images:
+        if (isinstance(im, torch.Tensor) and im.dtype == torch.uint8 and im.device == dev and im.shape == shape
+                and im.stride() == strides):
+            continue
+        if _rgb_geometry(im) != geo or (same_device and im.device != dev):
+            raise ValueError(message)
+    return geo
 
 
 def mtb_status_string(status: int) -> str:
@@ -436,10 +455,7 @@ def mtb_align_stack(images, levels: int, exclude_range: int = 4, ref_index: int 
     n = len(images)
     if not 1 <= n <= MTB_MAX_STACK:
         raise ValueError(f"a stack holds 1..{MTB_MAX_STACK} images")
-    W, H, stride = _rgb_geometry(images[0])
-    for im in images:
-        if _rgb_geometry(im) != (W, H, stride) or im.device != images[0].device:
-            raise ValueError("all images of a stack must share size, stride and device")
+    W, H, stride = _stack_geometry(images, "all images of a stack must share size, stride and device")
     dev = images[0].device
     need = (mtb_stack_bytemaps_workspace_bytes if _entry == "mtb_align_stack_bytemaps"
             else mtb_stack_workspace_bytes)(n, W, H, levels)
@@ -467,10 +483,7 @@ def mtb_tune_stack(images, levels: int, exclude_range: int = 4, ref_index: int =
     n = len(images)
     if not 1 <= n <= MTB_MAX_STACK:
         raise ValueError(f"a stack holds 1..{MTB_MAX_STACK} images")
-    W, H, stride = _rgb_geometry(images[0])
-    for im in images:
-        if _rgb_geometry(im) != (W, H, stride) or im.device != images[0].device:
-            raise ValueError("all images of a stack must share size, stride and device")
+    W, H, stride = _stack_geometry(images, "all images of a stack must share size, stride and device")
     dev = images[0].device
     workspace = _buffer(max(mtb_stack_workspace_bytes(n, W, H, levels), 1), dev, workspace)
     if shifts is None:
@@ -556,21 +569,15 @@ def mtb_apply_shifts(images, shifts: torch.Tensor, fill: int = MTB_FILL_ZERO, ou
     n = len(images)
     if not 1 <= n <= MTB_MAX_STACK:
         raise ValueError(f"a stack holds 1..{MTB_MAX_STACK} images")
-    W, H, stride = _rgb_geometry(images[0])
-    for im in images:
-        if _rgb_geometry(im) != (W, H, stride):
-            raise ValueError("all images must share size and stride")
+    W, H, stride = _stack_geometry(images, "all images must share size and stride", same_device=False)
     if (not isinstance(shifts, torch.Tensor) or not shifts.is_cuda or shifts.dtype != torch.int32
             or tuple(shifts.shape) != (n, 2) or not shifts.is_contiguous()):
         raise ValueError("shifts must be a contiguous int32 device tensor of shape (n, 2)")
     if out is None:
         out = [torch.empty((H, W, 3), dtype=torch.uint8, device=images[0].device) for _ in range(n)]
-    ostride = None
-    for o in out:
-        ow, oh, os_ = _rgb_geometry(o)
-        if (ow, oh) != (W, H) or (ostride is not None and os_ != ostride):
-            raise ValueError("outputs must match the inputs' size and share a stride")
-        ostride = os_
+    ow, oh, ostride = _stack_geometry(out, "outputs must match the inputs' size and share a stride", same_device=False)
+    if (ow, oh) != (W, H):
+        raise ValueError("outputs must match the inputs' size and share a stride")
     ins = (ctypes.c_void_p * n)(*[im.data_ptr() for im in images])
     outs = (ctypes.c_void_p * n)(*[o.data_ptr() for o in out])
     _check("mtb_apply_shifts",
@@ -627,11 +634,8 @@ def _batch_items(pairs):
         raise ValueError(f"a batch holds 1..{MTB_MAX_BATCH} items")
     items = (_BatchItem * n)()
     for i, (ref, mov, levels) in enumerate(pairs):
-        geo = _rgb_geometry(ref)
-        if _rgb_geometry(mov) != geo or mov.device != ref.device:
-            raise ValueError("the two images of an item must share size, stride and device")
-        W, H, stride = geo
-        items[i] = _BatchItem(ref.data_ptr(), mov.data_ptr(), stride, W, H, int(levels), 0)
+        W, H, stride = _stack_geometry((ref, mov), "the two images of an item must share size, stride and device")
+        items[i] = (ref.data_ptr(), mov.data_ptr(), stride, W, H, int(levels), 0)
     return items
 
 
@@ -675,11 +679,7 @@ def _batch_stacks(stacks):
         ref = -1 if len(st) < 3 or st[2] is None else int(st[2])
         if not 1 <= len(images) <= MTB_MAX_STACK:
             raise ValueError(f"a stack holds 1..{MTB_MAX_STACK} images")
-        geo = _rgb_geometry(images[0])
-        for im in images[1:]:
-            if _rgb_geometry(im) != geo or im.device != images[0].device:
-                raise ValueError("the images of a stack must share size, stride and device")
-        W, H, stride = geo
+        W, H, stride = _stack_geometry(images, "the images of a stack must share size, stride and device")
         ptrs = (ctypes.c_void_p * len(images))(*[im.data_ptr() for im in images])
         keep.append(ptrs)
         items[i] = _BatchStack(ctypes.cast(ptrs, ctypes.POINTER(ctypes.c_void_p)), len(images), ref, stride, W, H,
