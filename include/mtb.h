@@ -277,8 +277,9 @@ mtb_status mtb_align_stack_chained(const uint8_t *const *h_d_rgb, int32_t n, int
  *   - the pyramid pass: workgroups as a percentage of one round of the
  *     workgroups the device holds at once, and how many horizontally
  *     adjacent 64x256 tiles a workgroup takes at a time (1, 2 or 4);
- *   - the bitmaps pass: workgroups as a percentage of one resident round, and
- *     wavefronts per workgroup (2, 4 or 8);
+ *   - the bitmaps pass: workgroups as a percentage of the built-in number (one
+ *     resident round, more for large launch sets), and wavefronts per
+ *     workgroup (2, 4 or 8);
  *   - the search: how many of the coarsest levels are searched over
  *     exhaustive windows (radius 1, 3, 7, 15, 31 from the coarsest down;
  *     -1: the built-in rule, up to three levels of at most 8192 words of

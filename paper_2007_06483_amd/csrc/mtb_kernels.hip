@@ -676,64 +676,91 @@ __device__ __forceinline__ uint32_t ge_bytes(uint32_t x, uint32_t xh, ByteGe c)
     return (x & d) | (c.sel & (x | d));
 }
 
-// Eight dwords d[k] holding pixels 4k .. 4k+3 (byte b = pixel 4k + b) are
-// transposed so that t[k] holds pixels k, k+8, k+16, k+24 (byte b = pixel 8b + k).
-// v_perm_b32 (__builtin_amdgcn_perm(hi, lo, sel)): selector byte values 0-3
-// pick bytes of lo, 4-7 bytes of hi.
-__device__ __forceinline__ void transpose8(const uint32_t *d, uint32_t *t)
-{
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {  // h = 0: dwords 0,2,4,6 -> t[0..3]; h = 1: 1,3,5,7 -> t[4..7]
-        const uint32_t A = __builtin_amdgcn_perm(d[2 + h], d[0 + h], 0x05010400u);  // d0.b0 d2.b0 d0.b1 d2.b1
-        const uint32_t B = __builtin_amdgcn_perm(d[2 + h], d[0 + h], 0x07030602u);  // d0.b2 d2.b2 d0.b3 d2.b3
-        const uint32_t C = __builtin_amdgcn_perm(d[6 + h], d[4 + h], 0x05010400u);  // d4.b0 d6.b0 d4.b1 d6.b1
-        const uint32_t D = __builtin_amdgcn_perm(d[6 + h], d[4 + h], 0x07030602u);  // d4.b2 d6.b2 d4.b3 d6.b3
-        t[4 * h + 0] = __builtin_amdgcn_perm(C, A, 0x05040100u);
-        t[4 * h + 1] = __builtin_amdgcn_perm(C, A, 0x07060302u);
-        t[4 * h + 2] = __builtin_amdgcn_perm(D, B, 0x05040100u);
-        t[4 * h + 3] = __builtin_amdgcn_perm(D, B, 0x07060302u);
-    }
-}
-
-// The three thresholds of a level, T: m + 1, E: m + X + 1 and max(m - X, 0),
-// as byte-wise comparison constants; keep_* clear a threshold above 255.
+// The three thresholds of a level, T: m + 1, E: m + X + 1 and max(m - X, 0), as
+// byte-wise comparison constants.  A threshold y above 255, which no pixel
+// reaches, has low bytes of 0x80: d is then x & 0x7f, and x & d has no bit 7.
 struct Thresholds {
-    uint32_t low_t, low_hi, low_lo, keep_t, keep_hi;
-    int nlow;  // how many thresholds are below 128 (lo <= t <= hi, so a prefix)
+    uint32_t low_t, low_hi, low_lo;
+    uint32_t sel_t, sel_hi, sel_lo;  // all ones for a threshold below 128
+    int nlow;                        // how many are below 128 (lo <= t <= hi, so a prefix)
 };
 __device__ __forceinline__ Thresholds thresholds(uint32_t m, uint32_t X)
 {
     const uint32_t yt = m + 1u, yhi = m + X + 1u, ylo = m > X ? m - X : 0u;
+    auto low = [](uint32_t y) { return (y < 256u ? y & 0x7fu : 0x80u) * 0x01010101u; };
     Thresholds c;
-    c.low_t = (yt & 0x7fu) * 0x01010101u;
-    c.low_hi = (yhi & 0x7fu) * 0x01010101u;
-    c.low_lo = (ylo & 0x7fu) * 0x01010101u;
-    c.keep_t = yt < 256u ? ~0u : 0u;
-    c.keep_hi = yhi < 256u ? ~0u : 0u;
+    c.low_t = low(yt);
+    c.low_hi = low(yhi);
+    c.low_lo = low(ylo);
+    c.sel_t = yt < 128u ? ~0u : 0u;
+    c.sel_hi = yhi < 128u ? ~0u : 0u;
+    c.sel_lo = ylo < 128u ? ~0u : 0u;
     c.nlow = (ylo < 128u) + (yt < 128u) + (yhi < 128u);
     return c;
 }
 
-// T and E bits of a lane's 32 transposed pixels (byte b of t[k] = pixel 8b + k)
-// with ge_bytes specialised on which thresholds are below 128: x >= y is bit 7
-// of x | d for y < 128 and of x & d otherwise (d = (x | 0x80808080) - low).
-// Bit 7 of byte b of each answer moves to bit 8b + k of the word.
+constexpr uint32_t kMarks = 0x80808080u;
+
+// For four pixels x (byte b = pixel b): bit 7 of byte b of t is T, of band is
+// lo <= x < hi (E is its complement); the other bits are zero.  ge_bytes
+// specialised on which thresholds are below 128: x >= y is bit 7 of x | d for
+// y < 128 and of x & d otherwise (d = (x | 0x80808080) - low).
 template <bool kLowT, bool kLowHi, bool kLowLo>
-__device__ __forceinline__ void te_bits(const uint32_t (&t)[8], const Thresholds &c, uint32_t &tw, uint32_t &ew)
+__device__ __forceinline__ void te_marks(uint32_t x, const Thresholds &c, uint32_t &t, uint32_t &band)
 {
-    tw = 0u;
-    ew = 0u;
+    const uint32_t xh = x | kMarks;
+    const uint32_t dt = xh - c.low_t, dhi = xh - c.low_hi, dlo = xh - c.low_lo;
+    t = (kLowT ? (x | dt) : (x & dt)) & kMarks;
+    band = (kLowLo ? (x | dlo) : (x & dlo)) & ~(kLowHi ? (x | dhi) : (x & dhi)) & kMarks;
+}
+
+// The same with the cases picked at run time.
+__device__ __forceinline__ void te_marks_any(uint32_t x, const Thresholds &c, uint32_t &t, uint32_t &band)
+{
+    const uint32_t xh = x | kMarks;
+    const uint32_t dt = xh - c.low_t, dhi = xh - c.low_hi, dlo = xh - c.low_lo;
+    const uint32_t glo = (x & dlo) | (c.sel_lo & (x | dlo)), ghi = (x & dhi) | (c.sel_hi & (x | dhi));
+    t = ((x & dt) | (c.sel_t & (x | dt))) & kMarks;
+    band = glo & ~ghi & kMarks;
+}
+
+// Eight pixels' marks as 128 times the byte whose bit p is pixel p's: byte dot
+// products with the bits' weights (each mark is 128).
+__device__ __forceinline__ uint32_t mark_bits8(uint32_t m0, uint32_t m1)
+{
+    return __builtin_amdgcn_udot4(m1, 0x80402010u, __builtin_amdgcn_udot4(m0, 0x08040201u, 0u, false), false);
+}
+
+// T and E bits of 4 kDwords consecutive pixels d (byte b of d[k] = pixel 4k + b).
+template <int kDwords, bool kLowT, bool kLowHi, bool kLowLo>
+__device__ __forceinline__ void te_bits_of(const uint32_t *d, const Thresholds &c, uint32_t &tw, uint32_t &ew)
+{
+    uint32_t ta[kDwords / 2], ba[kDwords / 2];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        const uint32_t x = t[k], xh = x | 0x80808080u;
-        const uint32_t dt = xh - c.low_t, dhi = xh - c.low_hi, dlo = xh - c.low_lo;
-        const uint32_t gt = kLowT ? (x | dt) : (x & dt);
-        const uint32_t ghi = kLowHi ? (x | dhi) : (x & dhi);
-        const uint32_t glo = kLowLo ? (x | dlo) : (x & dlo);
-        const uint32_t rt = gt & c.keep_t;
-        const uint32_t re = (ghi & c.keep_hi) | ~glo;
-        tw |= (rt >> (7 - k)) & (0x01010101u << k);
-        ew |= (re >> (7 - k)) & (0x01010101u << k);
+    for (int k = 0; k < kDwords; k += 2) {
+        uint32_t t0, t1, b0, b1;
+        te_marks<kLowT, kLowHi, kLowLo>(d[k], c, t0, b0);
+        te_marks<kLowT, kLowHi, kLowLo>(d[k + 1], c, t1, b1);
+        ta[k / 2] = mark_bits8(t0, t1);
+        ba[k / 2] = mark_bits8(b0, b1);
+    }
+    if constexpr (kDwords == 8) {
+        tw = ((ta[0] + (ta[1] << 8) + (ta[2] << 16)) >> 7) | (ta[3] << 17);
+        ew = ~(((ba[0] + (ba[1] << 8) + (ba[2] << 16)) >> 7) | (ba[3] << 17));
+    } else {
+        tw = (ta[0] + (ta[1] << 8)) >> 7;
+        ew = ~((ba[0] + (ba[1] << 8)) >> 7);
+    }
+}
+
+template <int kDwords>
+__device__ __forceinline__ void te_bits(const uint32_t *d, const Thresholds &c, uint32_t &tw, uint32_t &ew)
+{
+    switch (c.nlow) {
+    case 0: te_bits_of<kDwords, false, false, false>(d, c, tw, ew); break;
+    case 1: te_bits_of<kDwords, false, false, true>(d, c, tw, ew); break;
+    case 2: te_bits_of<kDwords, true, false, true>(d, c, tw, ew); break;
+    default: te_bits_of<kDwords, true, true, true>(d, c, tw, ew); break;
     }
 }
 
@@ -741,10 +768,10 @@ __device__ __forceinline__ void te_bits(const uint32_t (&t)[8], const Thresholds
 // consecutive 64-pixel words of one level (the next chunk's loads are issued
 // before the current one is processed).  Lane i takes the chunk's bytes
 // [32 i, 32 i + 32), i.e. half-word i of the chunk, and forms its 32 T and E
-// bits in registers: four pixels per dword compared at once (ByteGe), after a
-// byte transpose that lets the per-byte answers be gathered into bit order
-// with one shift and one and-or per dword.  Lane i then stores dword i of the
-// chunk's T words and of its E words.  This walks chunks c0 .. c1 - 1 of
+// bits in registers: four pixels per dword compared at once (te_marks), the
+// answers gathered eight at a time by byte dot products with the bits' weights
+// (mark_bits8).  Lane i then stores dword i of the chunk's T words and of its
+// E words.  This walks chunks c0 .. c1 - 1 of
 // levels l0 .. L-1 of every image (per_image chunks each).
 __device__ __forceinline__ void walk_chunks(const BitmapArgs &a, int64_t c0, int64_t c1, int64_t per_image, int l0,
                                             int lane)
@@ -779,15 +806,8 @@ __device__ __forceinline__ void walk_chunks(const BitmapArgs &a, int64_t c0, int
             next_chunk(a, p, col0, l0);
             load_chunk(a, p, lane, v0, v1);
         }
-        uint32_t t[8];
-        transpose8(d, t);
         uint32_t tw, ew;
-        switch (th.nlow) {
-        case 0: te_bits<false, false, false>(t, th, tw, ew); break;
-        case 1: te_bits<false, false, true>(t, th, tw, ew); break;
-        case 2: te_bits<true, false, true>(t, th, tw, ew); break;
-        default: te_bits<true, true, true>(t, th, tw, ew); break;
-        }
+        te_bits<8>(d, th, tw, ew);
         // Bits past the level width are zero: lane i holds half-word i % 2 of
         // word w0 + i / 2, whose pixels start at column 64 * ((w0 + i / 2) mod wpr).
         int col = ccol0 + (lane >> 1);
@@ -804,51 +824,25 @@ __device__ __forceinline__ void walk_chunks(const BitmapArgs &a, int64_t c0, int
     }
 }
 
-// T and E answers of four pixels (byte b = pixel b) in bit 7 of each byte,
-// the case of te_bits picked at run time.
-__device__ __forceinline__ void te4(uint32_t x, const Thresholds &c, uint32_t &rt, uint32_t &re)
-{
-    const uint32_t xh = x | 0x80808080u;
-    const uint32_t dt = xh - c.low_t, dhi = xh - c.low_hi, dlo = xh - c.low_lo;
-    const uint32_t sl = c.nlow >= 1 ? ~0u : 0u, st = c.nlow >= 2 ? ~0u : 0u, sh = c.nlow >= 3 ? ~0u : 0u;
-    const uint32_t glo = (x & dlo) | (sl & (x | dlo));
-    const uint32_t gt = (x & dt) | (st & (x | dt));
-    const uint32_t ghi = (x & dhi) | (sh & (x | dhi));
-    rt = gt & c.keep_t;
-    re = (ghi & c.keep_hi) | ~glo;
-}
-
-// Bit 7 of byte b of r0 moved to bit b and bit 7 of byte b of r1 to bit 4 + b.
-// After the shifts byte b holds r0's bit at 8b and r1's at 8b + 4; the
-// product takes them to 24 + b and 28 + b (0x01020408 = 2^24 + 2^17 + 2^10 +
-// 2^3), and every other partial product lands below bit 24 or above bit 31,
-// each on a bit of its own, so nothing carries into bits 24..31.
-__device__ __forceinline__ uint32_t bits8(uint32_t r0, uint32_t r1)
-{
-    const uint32_t u = ((r0 >> 7) & 0x01010101u) | ((r1 >> 3) & 0x10101010u);
-    return (u * 0x01020408u) >> 24;
-}
-
 // The 8 level-1 pixels below a lane's 2 x 16 level-0 pixels of a pair unit
 // (d[0..3] row 2j, d[4..7] row 2j + 1, byte b of d[k] = pixel 4k + b): the
 // floor means of the 2x2 blocks, pixels 4h .. 4h + 3 in bytes 0..3 of g1[h].
-// Per dword pair: 16-bit sums of pixels (4k, 4k + 1) and (4k + 2, 4k + 3) of
-// both rows (bytes 1 and 3 moved down by a v_perm_b32 whose selector 0x0c
-// yields zero bytes), a quarter of each in byte 0 and byte 2 (sums are at
-// most 1020, so the shift leaves each in its own byte), then bytes 0 and 2
-// of two such dwords gathered by one more v_perm_b32.
+// A byte dot product with weights 64 leaves 64 times a block's sum, whose byte
+// 1 is a quarter of the sum (at most 255).
 __device__ __forceinline__ void level1_gray(const uint32_t (&d)[8], uint32_t (&g1)[2])
 {
-    uint32_t q[4];
+    uint32_t q[8];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-        const uint32_t a = d[k], b = d[k + 4];
-        const uint32_t sum = (a & 0x00ff00ffu) + __builtin_amdgcn_perm(0u, a, 0x0c030c01u) + (b & 0x00ff00ffu) +
-                             __builtin_amdgcn_perm(0u, b, 0x0c030c01u);
-        q[k] = sum >> 2;
+        q[2 * k] = __builtin_amdgcn_udot4(d[k], 0x00004040u, __builtin_amdgcn_udot4(d[k + 4], 0x00004040u, 0u, false),
+                                          false);
+        q[2 * k + 1] = __builtin_amdgcn_udot4(d[k], 0x40400000u,
+                                              __builtin_amdgcn_udot4(d[k + 4], 0x40400000u, 0u, false), false);
     }
-    g1[0] = __builtin_amdgcn_perm(q[1], q[0], 0x06040200u);
-    g1[1] = __builtin_amdgcn_perm(q[3], q[2], 0x06040200u);
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+        g1[h] = __builtin_amdgcn_perm(__builtin_amdgcn_perm(q[4 * h + 3], q[4 * h + 2], 0x0c0c0501u),
+                                      __builtin_amdgcn_perm(q[4 * h + 1], q[4 * h], 0x0c0c0501u), 0x05040100u);
 }
 
 // Segments of kPairWords words in a level-0 row.
@@ -896,23 +890,23 @@ __device__ __forceinline__ void pair_unit(const BitmapArgs &a, int img, int j, i
     }
     if (!row1)
         return;  // level 1 has floor(h / 2) rows
-    uint32_t rt0, re0, rt1, re1;
-    te4(g1[0], th1, rt0, re0);
-    te4(g1[1], th1, rt1, re1);
+    uint32_t t0, b0, t1, b1;
+    te_marks_any(g1[0], th1, t0, b0);
+    te_marks_any(g1[1], th1, t1, b1);
     const int x1 = x >> 1;
     const int nb1 = l1.w - x1;
     const uint32_t keep1 = nb1 >= 8 ? 0xffu : (nb1 <= 0 ? 0u : (1u << nb1) - 1u);
     if ((x1 >> 6) < l1.wpr) {
         const int64_t o1 = (int64_t)j * l1.wpr * 8 + (x1 >> 3);
-        bm[l1.tb_off + o1] = (uint8_t)(bits8(rt0, rt1) & keep1);
-        bm[l1.eb_off + o1] = (uint8_t)(bits8(re0, re1) & keep1);
+        bm[l1.tb_off + o1] = (uint8_t)((mark_bits8(t0, t1) >> 7) & keep1);
+        bm[l1.eb_off + o1] = (uint8_t)(~(mark_bits8(b0, b1) >> 7) & keep1);
     }
 }
 
 // Walks pair units c0 .. c1 - 1 (a.chunk_start[1] per image, images one
 // after another).  Each unit is two level-0 rows by kPairWords words: lane i
-// takes 16 pixels of each row, the same 32-pixel transpose and compare as a
-// chunk give their level-0 T and E bits (row 2j in the low half), and the
+// takes 16 pixels of each row, the same 32-pixel compare as a
+// chunk gives their level-0 T and E bits (row 2j in the low half), and the
 // 2x2 means of the same pixels give the 8 level-1 pixels below them, so that
 // level 1's gray is never read.
 __device__ __forceinline__ void walk_units(const BitmapArgs &a, int64_t c0, int64_t c1, int lane)
@@ -960,20 +954,16 @@ __device__ __forceinline__ void walk_units(const BitmapArgs &a, int64_t c0, int6
         }
         uint32_t g1[2];
         level1_gray(d, g1);
-        uint32_t t[8];
-        transpose8(d, t);
         uint32_t tw, ew;
-        switch (th0.nlow) {
-        case 0: te_bits<false, false, false>(t, th0, tw, ew); break;
-        case 1: te_bits<false, false, true>(t, th0, tw, ew); break;
-        case 2: te_bits<true, false, true>(t, th0, tw, ew); break;
-        default: te_bits<true, true, true>(t, th0, tw, ew); break;
-        }
+        te_bits<8>(d, th0, tw, ew);
         pair_unit(a, ci, cj, cs, lane, g1, tw, ew, th1);
     }
 }
 
-// The bitmaps pass.  Without kPairs every level is walked in chunks.  With
+// The bitmaps pass.  Bound by HBM: 7 x 6000x4000 takes 54 us for 238 MB (4.4
+// TB/s; the plain 4:1 stream reaches 5.35; 57 us before the dot products and
+// the shorter runs), 9 x 8485x5657 129 us for 612 MB (151).  Without kPairs every
+// level is walked in chunks.  With
 // kPairs (a.pairs; at least two levels) the launch's items are first every
 // image's pair units, which yield levels 0 and 1, then every image's chunks
 // of levels 2 .. L-1; a wavefront takes a contiguous run of items.
@@ -2418,12 +2408,22 @@ hipError_t launch_search_bytes(SearchArgs a, int cus, hipStream_t s)
     return hipSuccess;
 }
 
+// A wavefront's items: one resident round of workgroups, or as many more as
+// leave each wavefront this many.  Workgroups started in order keep the device
+// on one front of addresses and even out the compute units; a wavefront's
+// start (two median scans) costs about an item.  With one round whatever the
+// size, 9 x 8485x5657 (45 items) took 23 us longer and 7 x 6000x4000 (14) 2-3;
+// 2.3 items each made 7 x 3001x1999 1 us slower.
+constexpr int kItemsPerWave = 4;
+
 template <int kW, bool kPairs>
 hipError_t launch_bitmaps_w(const BitmapArgs &a, int cus, hipStream_t s, int blocks_pct)
 {
     const int64_t total = a.chunk_start[a.g.L] * a.n;
     int64_t blocks = (total + kW - 1) / kW;
-    const int64_t cap = (int64_t)cus * resident_per_cu<k_bitmaps<kW, kPairs>, 64 * kW>() * blocks_pct / 100;
+    const int64_t round = (int64_t)cus * resident_per_cu<k_bitmaps<kW, kPairs>, 64 * kW>();
+    const int64_t most = total / (kW * kItemsPerWave);
+    const int64_t cap = (most > round ? most : round) * blocks_pct / 100;
     blocks = blocks > cap ? cap : (blocks < 1 ? 1 : blocks);
     return launch_kernel("k_bitmaps", k_bitmaps<kW, kPairs>, dim3((unsigned)blocks), dim3(64 * kW), s, a);
 }
