@@ -684,9 +684,7 @@ mtb_status align_pair_in(const void *d_bm_ref, const void *d_bm_mov, const Geome
 
 // One pair's search state and tickets for the most levels a call takes.
 constexpr int64_t kPairScratchWords =
-    (((int64_t)kMaxLevels * kCounterWords + 2 * kMaxLevels + kSurfWords + kAlign / 4 - 1) / (kAlign / 4)) *
-        (kAlign / 4) +
-    kTicketWords;
+    (pair_state_words(kMaxLevels) + kAlign / 4 - 1) / (kAlign / 4) * (kAlign / 4) + kTicketWords;
 
 // A batch's groups run on up to kBatchLanes streams of the library at once
 // (forked from and joined back to the caller's stream with events), each

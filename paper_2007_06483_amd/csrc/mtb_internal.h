@@ -30,11 +30,13 @@ constexpr int kMergeMinWgsPerImage = 192;
 constexpr int kTileH = 64;
 constexpr int kTileW = 256;
 
-// Search counters are spread over this many copies per (pair, level) so that
-// concurrent workgroups do not all add into the same nine words.
-constexpr int kCopies = 16;
-// Per pair and level: kCopies x 9 uint32 counters.
-constexpr int kCounterWords = kCopies * 9;
+// Search counters are spread over this many copies per (pair, level), so that
+// concurrent workgroups do not all add into the same nine words, each copy 64
+// bytes from the next: atomics that share a cache line queue (16 packed copies
+// made a 4096x3072 pair 0.9 us slower, 16 copies 128 bytes apart take longer to
+// read back).
+constexpr int kCopies = 8;
+constexpr int kCounterStride = 16;  // words from one copy to the next
 
 inline int64_t align_up(int64_t v, int64_t a) { return (v + a - 1) / a * a; }
 
@@ -122,12 +124,20 @@ constexpr int kCoarseLevels = 5;
 constexpr int kSurfWords = 3 * 3 + 7 * 7 + 15 * 15 + 31 * 31 + 63 * 63;
 constexpr int kLdsSurfWords = 3 * 3 + 7 * 7 + 15 * 15;
 
-// Per pair the search state is: counters uint32[L][kCounterWords], then
-// base int32[L][2] (the centre of each level's nine candidates), then the
-// coarse error surfaces uint32[kSurfWords].  After every pair's state come the
-// ticket counters of the coarse launch and of the level-0 launch: each
-// kTicketGroups group counters and one counter of completed groups.
-inline int64_t pair_state_words(int32_t L) { return (int64_t)L * kCounterWords + 2 * L + kSurfWords; }
+// Per pair the search state is: base int32[L][2] (the centre of each level's
+// nine candidates), the coarse error surfaces uint32[kSurfWords], then on a
+// 64-byte boundary the counters uint32[L][kCopies][kCounterStride].  After
+// every pair's state come the ticket counters of the coarse launch and of the
+// level-0 launch: each kTicketGroups group counters and one counter of
+// completed groups.
+constexpr int pair_counter_offset(int32_t L)
+{
+    return (2 * L + kSurfWords + kCounterStride - 1) / kCounterStride * kCounterStride;
+}
+// Each level counts for 146 words, which also cover the boundary's padding.
+constexpr int64_t pair_state_words(int32_t L) { return (int64_t)L * 146 + kSurfWords; }
+static_assert(pair_counter_offset(1) + kCopies * kCounterStride <= pair_state_words(1), "one level's counters fit");
+static_assert(146 >= kCopies * kCounterStride + 2, "every further level's counters fit");
 constexpr int kTicketGroups = 32;
 constexpr int kTicketWords = 2 * (kTicketGroups + 1);
 
@@ -252,6 +262,9 @@ int coarse_level_count(const Geometry &g, int npairs);
 // (for a stream width cw_log2, 0: the rule).
 int search_rows_rule(const Geometry &g, int l, int npairs, int device_cus, int cw_log2 = 0);
 int search_row_blocks(const Geometry &g, int l, int rows, int cw_log2 = 0);
+// Rows per lane of a fine level searched one word a lane (0: by k_search_fine).
+int search_pos_rows(const Geometry &g, int l, int npairs, int device_cus);
+int search_pos_blocks(const Geometry &g, int l, int rows);
 // Coarse levels a search runs with shape t (null: the rule).
 int coarse_levels_used(const Geometry &g, int npairs, const LaunchTune *t);
 // A pair whose two bitmap pyramids (every plane, as laid out in the bitmaps

@@ -4,7 +4,8 @@
 //         k_pyramid_coarse  levels 7.. from level 6 (one workgroup per image)
 // Pass 2  k_bitmaps         gray -> lower median per level, packed T/E words
 // Search  k_search_coarse   small levels, one workgroup per pair, all in one launch
-//         k_search_fine     one launch per large level, grid over (units, pairs);
+//         k_search_pos      one launch per finer level while a lane can take one word of it,
+//         k_search_fine     beyond that units of rows; grid over (workgroups, pairs);
 //                           the last workgroup of the level-0 launch writes the results
 //
 // The arithmetic is integer throughout; reductions are integer adds, so the
@@ -1333,14 +1334,17 @@ __device__ __forceinline__ uint32_t *pair_state(const SearchArgs &a, int p)
     return a.state + (int64_t)p * a.state_stride;
 }
 
-__device__ __forceinline__ int32_t *pair_bases(const SearchArgs &a, int p)
-{
-    return (int32_t *)(pair_state(a, p) + (int64_t)a.g.L * kCounterWords);
-}
+__device__ __forceinline__ int32_t *pair_bases(const SearchArgs &a, int p) { return (int32_t *)pair_state(a, p); }
 
 __device__ __forceinline__ uint32_t *pair_surface(const SearchArgs &a, int p)
 {
-    return pair_state(a, p) + (int64_t)a.g.L * kCounterWords + 2 * a.g.L;
+    return pair_state(a, p) + 2 * a.g.L;
+}
+
+// Copy c of level l's nine counters.
+__device__ __forceinline__ uint32_t *pair_counters(const SearchArgs &a, int p, int l, int c)
+{
+    return pair_state(a, p) + pair_counter_offset(a.g.L) + (l * kCopies + c) * kCounterStride;
 }
 
 // Radius of the exhaustive window at the i-th coarsest level, and where its
@@ -1372,16 +1376,16 @@ __device__ __forceinline__ void write_level(const SearchArgs &a, int p, int l, c
 }
 
 // Level 0's outputs for every pair, from its counters (the sum of their
-// kCopies copies) and base.  Run by the last workgroup of the level-0 launch.
+// copies) and base.  Run by the last workgroup of the level-0 launch.
 __device__ void finalize_level0(const SearchArgs &a)
 {
     __shared__ uint32_t tot[kMaxStack * 9];
     for (int i = threadIdx.x; i < a.npairs * 9; i += blockDim.x) {
-        const uint32_t *cnt = pair_state(a, i / 9) + i % 9;
+        const uint32_t *cnt = pair_counters(a, i / 9, 0, 0) + i % 9;
         uint32_t s = 0;
 #pragma unroll
         for (int k = 0; k < kCopies; ++k)
-            s += load_shared(cnt + 9 * k);
+            s += load_shared(cnt + k * kCounterStride);
         tot[i] = s;
     }
     __syncthreads();
@@ -1631,12 +1635,11 @@ __global__ __launch_bounds__(256) void k_search_coarse(SearchArgs a)
 // every thread of the workgroup; ends with a workgroup barrier.
 __device__ __forceinline__ void level_base(const SearchArgs &a, int pair, int *sbase)
 {
-    __shared__ uint32_t cnt[kLdsSurfWords > kCounterWords ? kLdsSurfWords : kCounterWords];
+    __shared__ uint32_t cnt[kLdsSurfWords > 9 * kCopies ? kLdsSurfWords : 9 * kCopies];
     __shared__ uint32_t tot[9];
     __shared__ int sprev[2];
     const Geometry &g = a.g;
     const int l = a.level;
-    uint32_t *state = pair_state(a, pair);
     int32_t *bases = pair_bases(a, pair);
 
     if (a.coarse_n > 0 && l == g.L - 1 - a.coarse_n) {
@@ -1661,17 +1664,18 @@ __device__ __forceinline__ void level_base(const SearchArgs &a, int pair, int *s
             sbase[1] = 2 * s.y;
         }
     } else if (l < g.L - 1) {
-        if (threadIdx.x < kCounterWords)
-            cnt[threadIdx.x] = state[(l + 1) * kCounterWords + threadIdx.x];
-        else if (threadIdx.x < kCounterWords + 2)
-            sprev[threadIdx.x - kCounterWords] = bases[2 * (l + 1) + threadIdx.x - kCounterWords];
+        const int w = threadIdx.x;
+        if (w < 9 * kCopies)
+            cnt[w] = pair_counters(a, pair, l + 1, w / 9)[w % 9];
+        else if (w < 9 * kCopies + 2)
+            sprev[w - 9 * kCopies] = bases[2 * (l + 1) + w - 9 * kCopies];
         __syncthreads();
-        if (threadIdx.x < 9) {
+        if (w < 9) {
             uint32_t s = 0;
 #pragma unroll
             for (int k = 0; k < kCopies; ++k)
-                s += cnt[k * 9 + threadIdx.x];
-            tot[threadIdx.x] = s;
+                s += cnt[k * 9 + w];
+            tot[w] = s;
         }
         __syncthreads();
         if (threadIdx.x == 0) {
@@ -1701,7 +1705,7 @@ __device__ __forceinline__ void level_base(const SearchArgs &a, int pair, int *s
 }
 
 // Sums the workgroup's nine errors into this level's counters (copy
-// blockIdx.x % kCopies); at level 0 the last workgroup writes the outputs.
+// blockIdx.x mod kCopies); at level 0 the last workgroup writes the outputs.
 __device__ __forceinline__ void level_finish(const SearchArgs &a, int pair, const uint32_t *acc)
 {
     __shared__ uint32_t red[4][9];
@@ -1721,7 +1725,7 @@ __device__ __forceinline__ void level_finish(const SearchArgs &a, int pair, cons
         const uint32_t s = red[0][threadIdx.x] + red[1][threadIdx.x] + red[2][threadIdx.x] +
                            red[3][threadIdx.x];
         if (s)
-            atomicAdd(pair_state(a, pair) + a.level * kCounterWords + (blockIdx.x % kCopies) * 9 + threadIdx.x, s);
+            atomicAdd(pair_counters(a, pair, a.level, blockIdx.x % kCopies) + threadIdx.x, s);
     }
     if (a.level == 0 && last_workgroup(a.done + kTicketGroups + 1))
         finalize_level0(a);
@@ -1740,6 +1744,91 @@ __global__ __launch_bounds__(256) void k_search_fine(SearchArgs a)
     if (unit < p.units)
         search_unit(a.ref[pair], a.mov[pair], lv, sbase[0], sbase[1], unit, p.cw_log2, a.rows_per_stream,
                     p.units_x, acc);
+    level_finish(a, pair, acc);
+}
+
+// The nine candidate errors of kRows rows of one reference word: column word k,
+// rows y0 .. y0 + kRows - 1 of the level.  Everything is loaded before anything
+// is scored: the reference rows and the kRows + 2 moving rows around them,
+// three words each, which are aligned to the first of the three horizontally
+// shifted copies.  Rows and columns outside the level are read clamped (the
+// layout keeps the two words either side of a row inside the buffer) and
+// their exclusion words masked.
+template <int kRows>
+__device__ __forceinline__ void search_pos(const uint8_t *ref, const uint8_t *mov, const LevelGeom &lv, int bx, int by,
+                                           int k, int y0, uint32_t *acc)
+{
+    typedef uint32_t U32x3 __attribute__((ext_vector_type(3), aligned(4)));
+    const int n32 = 2 * lv.wpr, h = lv.h;
+    const uint32_t row_bytes = 4u * (uint32_t)n32;
+    const int u = -bx - 1;  // bit offset of copy ddx = +1 from the word's first column
+    const uint32_t r = (uint32_t)u & 31u;
+    const int q = k + (u >> 5);  // arithmetic shift: the first moving word
+    const uint32_t coff = 4u * (uint32_t)((q < -2 ? -2 : (q > n32 - 1 ? n32 - 1 : q)) + 2);
+    const uint8_t *tr = ref + lv.tb_off + 4 * k, *er = ref + lv.eb_off + 4 * k;
+    const uint8_t *tm = mov + lv.tb_off - 8 + coff, *em = mov + lv.eb_off - 8 + coff;
+    uint32_t rt[kRows], re[kRows];
+    U32x3 mt[kRows + 2], me[kRows + 2];
+#pragma unroll
+    for (int i = 0; i < kRows; ++i) {
+        const uint32_t ro = (uint32_t)(y0 + i < h ? y0 + i : h - 1) * row_bytes;
+        rt[i] = *(const uint32_t *)(tr + ro);
+        re[i] = *(const uint32_t *)(er + ro);
+    }
+#pragma unroll
+    for (int i = 0; i < kRows + 2; ++i) {
+        const int j = y0 - by - 1 + i;
+        const uint32_t mo = (uint32_t)(j < 0 ? 0 : (j >= h ? h - 1 : j)) * row_bytes;
+        mt[i] = *(const U32x3 *)(tm + mo);
+        me[i] = *(const U32x3 *)(em + mo);
+    }
+    uint32_t cm[3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+        cm[i] = (q + i >= 0 && q + i < n32) ? ~0u : 0u;
+#pragma unroll
+    for (int i = 0; i < kRows; ++i)
+        re[i] = y0 + i < h ? re[i] : 0u;
+#pragma unroll
+    for (int i = 0; i < kRows + 2; ++i) {
+        const uint32_t rm = (uint32_t)(y0 - by - 1 + i) < (uint32_t)h ? ~0u : 0u;
+        const uint32_t e0 = me[i].x & cm[0] & rm, e1 = me[i].y & cm[1] & rm, e2 = me[i].z & cm[2] & rm;
+        const uint32_t t0 = funnel(mt[i].y, mt[i].x, r), t1 = funnel(mt[i].z, mt[i].y, r);
+        const uint32_t s0 = funnel(e1, e0, r), s1 = funnel(e2, e1, r);
+        const uint32_t st[3] = {t0, funnel(t1, t0, 1), funnel(t1, t0, 2)};  // ddx = 1 - d
+        const uint32_t se[3] = {s0, funnel(s1, s0, 1), funnel(s1, s0, 2)};
+#pragma unroll
+        for (int v = 0; v < 3; ++v) {  // reference row y0 + i - v meets this row at ddy = 1 - v
+            const int y = i - v;
+            if (y < 0 || y >= kRows)
+                continue;
+#pragma unroll
+            for (int d = 0; d < 3; ++d)
+                acc[3 * (2 - v) + 2 - d] += __builtin_popcount((rt[y] ^ st[d]) & re[y] & se[d]);
+        }
+    }
+}
+
+// One level below the coarse ones for every pair, as k_search_fine, for levels
+// small enough to give each lane one word of kRows (1, 2 or 4) rows: grid
+// (workgroups per pair, pairs).  Such a level is bound by the latency of its
+// chain (the previous level's counters, the base, the bitmaps, the sums), and
+// a stream of four rows of two words, the least k_search_fine takes, adds 1 us
+// of vector work to it: levels 2 and 1 of a 4096x3072 pair 6.7 and 5.5 -> 4.9
+// and 4.7 us.
+template <int kRows>
+__global__ __launch_bounds__(256) void k_search_pos(SearchArgs a)
+{
+    __shared__ int sbase[2];
+    const int pair = blockIdx.y;
+    level_base(a, pair, sbase);
+    const LevelGeom &lv = a.g.lv[a.level];
+    const int n32 = 2 * lv.wpr;
+    const int p = blockIdx.x * 256 + threadIdx.x;
+    const int yb = p / n32, k = p - yb * n32;
+    uint32_t acc[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+    if (yb * kRows < lv.h)
+        search_pos<kRows>(a.ref[pair], a.mov[pair], lv, sbase[0], sbase[1], k, yb * kRows, acc);
     level_finish(a, pair, acc);
 }
 
@@ -2487,6 +2576,31 @@ int search_rows_rule(const Geometry &g, int l, int npairs, int cus, int cw_log2)
     return rows;
 }
 
+// Workgroups per pair of a fine level whose lanes take one word of `rows` rows
+// (a multiple of kXcds, as in search_row_blocks).
+int search_pos_blocks(const Geometry &g, int l, int rows)
+{
+    const int64_t lanes = (int64_t)2 * g.lv[l].wpr * ((g.lv[l].h + rows - 1) / rows);
+    return (int)(((lanes + 255) / 256 + kXcds - 1) / kXcds * kXcds);
+}
+
+// Rows per lane of a fine level that k_search_pos takes, or 0 if the level is
+// k_search_fine's: the fewest that keep the grid within one workgroup a
+// compute unit.  Beyond that the workgroups' counter atomics, and at level 0
+// their tickets, cost more than the shorter chains give: at level 0 of a
+// 4096x3072 pair 192 workgroups of k_search_fine take 7.9 us, 768 of one word
+// by two rows 10.4; two a compute unit made 5 x 2449x1633 1 us slower, one
+// makes it 2.5 faster (66.7 -> 64.2 us).
+constexpr int kPosBlocksPerCu = 1;
+
+int search_pos_rows(const Geometry &g, int l, int npairs, int cus)
+{
+    for (int rows = 1; rows <= 4; rows *= 2)
+        if ((int64_t)search_pos_blocks(g, l, rows) * npairs <= (int64_t)kPosBlocksPerCu * cus)
+            return rows;
+    return 0;
+}
+
 int coarse_levels_used(const Geometry &g, int npairs, const LaunchTune *t)
 {
     if (!t || t->coarse < 0)
@@ -2521,8 +2635,17 @@ hipError_t launch_search(SearchArgs a, int cus, hipStream_t s, const LaunchTune 
     }
     for (int l = g.L - 1 - cn; l >= 0; --l) {
         const int cw = t ? t->cw[l] : 0;
-        const int rows = t && t->rows[l] > 0 ? t->rows[l] : search_rows_rule(g, l, a.npairs, cus, cw);
         a.level = l;
+        const int pos = t && (t->rows[l] > 0 || cw > 0) ? 0 : search_pos_rows(g, l, a.npairs, cus);
+        if (pos > 0) {
+            const dim3 grid(search_pos_blocks(g, l, pos), a.npairs);
+            e = launch_kernel("k_search_pos", pos == 1 ? k_search_pos<1> : pos == 2 ? k_search_pos<2> : k_search_pos<4>,
+                              grid, dim3(256), s, a);
+            if (e != hipSuccess)
+                return e;
+            continue;
+        }
+        const int rows = t && t->rows[l] > 0 ? t->rows[l] : search_rows_rule(g, l, a.npairs, cus, cw);
         a.rows_per_stream = rows;
         a.cw_log2 = cw;
         e = launch_kernel("k_search_fine", k_search_fine, dim3(search_row_blocks(g, l, rows, cw), a.npairs),

@@ -7,6 +7,7 @@ import numpy as np
 import pytest
 
 import oracle
+import synth
 from mtb_decode import bitmaps, gray_levels, histograms, medians, stack_workspace
 
 pytestmark = pytest.mark.gpu
@@ -114,3 +115,28 @@ def test_pyramid_claimed_tiles(mtb, n, w, h, pct, group):
                     assert np.array_equal(g, want.gray(l)), f"gray level {l}"
     finally:
         mtb.mtb_tune_reset()
+
+
+# A fine level is searched one word a lane, 1, 2 or 4 rows each, while that
+# takes at most one workgroup a compute unit (65536 lanes), else in row
+# streams: sizes whose levels 0 to 2 fall on every side of those limits, rows
+# of 1 to 40 words, heights that are no multiple of the rows, many pairs, and
+# shifts that move words across the row's ends.
+@pytest.mark.parametrize("n,w,h,L", [(2, 1300, 1250, 5), (2, 2000, 1030, 6), (2, 2049, 2051, 6), (3, 700, 2901, 6),
+                                     (9, 640, 403, 5), (5, 1111, 777, 6), (2, 129, 4000, 5), (32, 300, 331, 4)])
+def test_fine_levels_one_word_a_lane(mtb, n, w, h, L):
+    imgs, _, _ = synth.make_stack(w, h, n, 12, 500 + w + n, min(1 << (L - 1), min(w, h) // 4), sat_frac=0.05)
+    d = [_view(im, 0, 0) for im in imgs]
+    mtb.mtb_tune_reset()
+    mtb.mtb_set_shape(n, w, h, 3 * w, L, {"small_search": 0, "coarse_levels": 0})
+    try:
+        alt = mtb.mtb_align_stack(d, L, trace=True)
+    finally:
+        mtb.mtb_tune_reset()
+    got = mtb.mtb_align_stack(d, L, trace=True)
+    torch.cuda.synchronize()
+    want = oracle.align_stack(imgs, L, threads=4, keep=False)
+    for r in (got, alt):
+        assert np.array_equal(r["shifts"].cpu().numpy(), want["shifts"])
+        assert np.array_equal(r["errs"].cpu().numpy().astype(np.int64), want["errs"])
+        assert np.array_equal(r["trace"].cpu().numpy(), got["trace"].cpu().numpy())
