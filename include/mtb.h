@@ -287,7 +287,7 @@ mtb_status mtb_align_stack_chained(const uint8_t *const *h_d_rgb, int32_t n, int
  *     and per fine level the rows each row stream covers
  *     and the lanes of a row stream (8, 16, 32 or 64; 0: the built-in rules,
  *     the fewest rows that keep one level's grid within one resident round
- *     and the width that pads rows least); and whether a pair whose two
+ *     and a wide stream that pads rows little); and whether a pair whose two
  *     bitmap pyramids fit 144 KiB (every plane of the bitmaps buffer, from
  *     the end of its leading 256-byte guard to the medians) is searched by one
  *     workgroup that holds both in LDS and runs every level in one launch

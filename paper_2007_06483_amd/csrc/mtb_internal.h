@@ -224,7 +224,7 @@ hipError_t launch_kernel(const char *name, void (*k)(A), dim3 grid, dim3 block, 
 // the coarsest levels are searched over exhaustive windows (-1: the rule);
 // and per fine level the rows per stream (0: the rule that keeps the grid
 // within one resident round) and the lanes per row stream (log2, 3 .. 6; 0:
-// the rule that pads rows least).
+// the rule that pads rows little).
 constexpr int kRowsStep = 4;   // rows per stream come in multiples of this
 constexpr int kRowsMax = 64;
 struct LaunchTune {

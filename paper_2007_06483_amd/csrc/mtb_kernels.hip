@@ -1111,8 +1111,11 @@ struct UnitPlan {
 __host__ __device__ __forceinline__ UnitPlan plan_level(const LevelGeom &lv, int rows, int cw_force)
 {
     const int cols = lv.wpr;  // two-word columns per row (n32 / 2)
-    // The stream width (8 .. 64 lanes) that pads the row least, ties going
-    // wide; cw_force (3 .. 6, a launch-shape knob) overrides it.
+    // The widest stream (8 .. 64 lanes) that pads the row by at most a quarter,
+    // or the one that pads it least: a wide stream's loads are whole cache
+    // lines (level 0 of 9 x 8485x5657, 134 columns: 32 lanes, a fifth padding,
+    // 616 -> 607 us a call against 8 lanes, which pad two columns).  cw_force
+    // (3 .. 6, a launch-shape knob) overrides it.
     int best = 6, best_pad = 1 << 30;
     for (int c = 6; c >= 3; --c) {
         const int pad = (((cols + (1 << c) - 1) >> c) << c) - cols;
@@ -1120,6 +1123,8 @@ __host__ __device__ __forceinline__ UnitPlan plan_level(const LevelGeom &lv, int
             best = c;
             best_pad = pad;
         }
+        if (4 * pad <= cols)
+            break;
     }
     if (cw_force >= 3 && cw_force <= 6)
         best = cw_force;

@@ -121,9 +121,11 @@ def test_pyramid_claimed_tiles(mtb, n, w, h, pct, group):
 # takes at most one workgroup a compute unit (65536 lanes), else in row
 # streams: sizes whose levels 0 to 2 fall on every side of those limits, rows
 # of 1 to 40 words, heights that are no multiple of the rows, many pairs, and
-# shifts that move words across the row's ends.
+# shifts that move words across the row's ends; rows of 134 two-word columns take
+# streams that pad them by a fifth.
 @pytest.mark.parametrize("n,w,h,L", [(2, 1300, 1250, 5), (2, 2000, 1030, 6), (2, 2049, 2051, 6), (3, 700, 2901, 6),
-                                     (9, 640, 403, 5), (5, 1111, 777, 6), (2, 129, 4000, 5), (32, 300, 331, 4)])
+                                     (9, 640, 403, 5), (5, 1111, 777, 6), (2, 129, 4000, 5), (32, 300, 331, 4),
+                                     (5, 8485, 300, 4)])
 def test_fine_levels_one_word_a_lane(mtb, n, w, h, L):
     imgs, _, _ = synth.make_stack(w, h, n, 12, 500 + w + n, min(1 << (L - 1), min(w, h) // 4), sat_frac=0.05)
     d = [_view(im, 0, 0) for im in imgs]
