@@ -672,6 +672,7 @@ mtb_status align_pair_in(const void *d_bm_ref, const void *d_bm_mov, const Geome
     a.npairs = 1;
     a.out.pair_image[0] = 0;
     a.out.n_out = 1;
+    a.out.chain_ref = -1;
     a.out.shifts = d_shift;
     a.out.errs = d_err;
     a.out.trace = d_trace;
@@ -765,9 +766,11 @@ Lanes *batch_lanes()
 // A batch: one launch set per group of units that share geometry and stride,
 // each with its key's tuned shape (or, for the key ov_key, the shape ov_shape);
 // rows output rows.  Units must be valid.
+// With quad_flag (four quadrant pairs) also enqueues the quadrant check.
 mtb_status align_units(const std::vector<BatchUnit> &u, int64_t rows, int32_t exclude_range, void *d_workspace,
                        size_t workspace_bytes, int32_t *d_shifts, uint32_t *d_errs, hipStream_t s,
-                       const TuneKey *ov_key, const LaunchTune *ov_shape)
+                       const TuneKey *ov_key, const LaunchTune *ov_shape, int32_t *quad_flag = nullptr,
+                       int32_t quad_tol = 0)
 {
     if (!d_workspace || !d_shifts || !d_errs || exclude_range < 0 || exclude_range > 255)
         return MTB_ERR_INVALID_ARG;
@@ -829,6 +832,7 @@ mtb_status align_units(const std::vector<BatchUnit> &u, int64_t rows, int32_t ex
         SearchOutputs out;
         memset(&out, 0, sizeof(out));
         out.n_out = (int32_t)rows;
+        out.chain_ref = -1;
         out.shifts = d_shifts;
         out.errs = d_errs;
         ZeroArgs z;
@@ -839,6 +843,11 @@ mtb_status align_units(const std::vector<BatchUnit> &u, int64_t rows, int32_t ex
             t = *ov_shape;
         else
             tune_lookup(key, &t);
+        if (quad_flag && ps.npairs == 4 && search_finalizes(g, ps.npairs, &t)) {
+            out.flag = quad_flag;
+            out.tol = quad_tol;
+            quad_flag = nullptr;  // the search forms it
+        }
         const int l = plan.lane[k];
         e = enqueue_set(ps, g, f.stride, exclude_range, ws + l * plan.lane_bytes, out, z, cus,
                         lanes ? lanes->s[l] : s, false, t);
@@ -850,6 +859,8 @@ mtb_status align_units(const std::vector<BatchUnit> &u, int64_t rows, int32_t ex
         for (int l = 0; l < plan.lanes; ++l)
             joined = hipEventRecord(lanes->done[l], lanes->s[l]) == hipSuccess &&
                      hipStreamWaitEvent(s, lanes->done[l], 0) == hipSuccess && joined;
+    if (e == hipSuccess && joined && quad_flag)
+        e = launch_quadrant_flag(d_shifts, quad_tol, quad_flag, s);
     return e == hipSuccess && joined ? MTB_OK : MTB_ERR_DEVICE;
 }
 
@@ -1162,6 +1173,7 @@ mtb_status align_stack(const uint8_t *const *h_d_rgb, int32_t n, int32_t width, 
     SearchOutputs out;
     memset(&out, 0, sizeof(out));
     out.n_out = n;
+    out.chain_ref = -1;
     out.shifts = d_shifts;
     out.errs = d_errs;
     out.trace = d_trace;
@@ -1182,8 +1194,11 @@ mtb_status align_stack(const uint8_t *const *h_d_rgb, int32_t n, int32_t width, 
         t = *shape;
     else if (!bytemaps)
         tune_lookup(tune_key(n, width, height, levels, row_stride), &t);
+    const bool fused = chained && search_finalizes(g, n - 1, &t);
+    if (fused)
+        out.chain_ref = ref;
     hipError_t e = enqueue_set(ps, g, row_stride, exclude_range, ws, out, z, cus, s, bytemaps, t);
-    if (e == hipSuccess && chained && n > 1)
+    if (e == hipSuccess && chained && n > 1 && !fused)
         e = launch_chain(d_shifts, n, ref, s);
     return device_status(e);
 }
@@ -1531,11 +1546,11 @@ mtb_status mtb_align_quadrants(const uint8_t *d_ref_rgb, const uint8_t *d_mov_rg
         return MTB_ERR_INVALID_ARG;
     if (workspace_bytes < need)
         return MTB_ERR_WORKSPACE;
-    const mtb_status st = mtb_align_batch(it, 4, exclude_range, d_workspace, workspace_bytes, d_shifts,
-                                          d_errs, stream);
-    if (st != MTB_OK)
-        return st;
-    return device_status(launch_quadrant_flag(d_shifts, tolerance, d_flag, (hipStream_t)stream));
+    std::vector<BatchUnit> u;
+    if (!pair_units(it, 4, &u))
+        return MTB_ERR_INVALID_ARG;
+    return align_units(u, 4, exclude_range, d_workspace, workspace_bytes, d_shifts, d_errs, (hipStream_t)stream, nullptr,
+                       nullptr, d_flag, tolerance);
 }
 
 }  // extern "C"

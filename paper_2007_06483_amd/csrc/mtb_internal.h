@@ -146,7 +146,9 @@ constexpr int kTicketWords = 2 * (kTicketGroups + 1);
 struct SearchOutputs {
     int32_t pair_image[kMaxStack];   // output row of each pair (stack index)
     int32_t n_out;                   // rows of the outputs
-    int32_t pad_;
+    int32_t chain_ref;               // -1, or (search_finalizes) a chained stack's reference: shifts are summed
+    int32_t tol, pad_;               // the quadrant check's tolerance
+    int32_t *flag;                   // NULL, or (search_finalizes) the quadrant check's flag
     int32_t *shifts;                 // [n_out][2]
     uint32_t *errs;                  // [n_out]
     uint32_t *trace;                 // NULL or [n_out][L][9]
@@ -274,6 +276,9 @@ constexpr int64_t kSmallLdsBytes = 144 * 1024;
 bool small_search_fits(const Geometry &g);
 // Whether launch_search takes the one-workgroup search with shape t (null: the rule).
 bool small_search_used(const Geometry &g, const LaunchTune *t);
+// Whether one launch of the search sees every pair's level-0 result, so that
+// it can sum a chained stack's shifts or form the quadrant flag itself.
+bool search_finalizes(const Geometry &g, int npairs, const LaunchTune *t);
 // t: the launch shape (rows and lanes per stream per level, coarse levels), or null for the rules.
 hipError_t launch_search(SearchArgs a, int device_cus, hipStream_t s, const LaunchTune *t = nullptr);
 

@@ -1374,17 +1374,37 @@ __device__ __forceinline__ void write_level(const SearchArgs &a, int p, int l, c
         o.level_shifts[(r * L + l) * 2 + 1] = sy;
     }
     if (l == 0) {
-        o.shifts[2 * r] = sx;
-        o.shifts[2 * r + 1] = sy;
+        if (o.chain_ref < 0) {
+            o.shifts[2 * r] = sx;
+            o.shifts[2 * r + 1] = sy;
+        }
         o.errs[r] = c[argmin9(c)];
     }
 }
 
+// Whether two of four shifts differ by more than tol along an axis.
+__device__ int32_t quadrants_differ(const int32_t (*s)[2], int32_t tol)
+{
+    int32_t f = 0;
+    for (int i = 0; i < 4; ++i)
+        for (int j = i + 1; j < 4; ++j)
+            for (int c = 0; c < 2; ++c) {
+                const int32_t d = s[i][c] - s[j][c];
+                if (d > tol || -d > tol)
+                    f = 1;
+            }
+    return f;
+}
+
 // Level 0's outputs for every pair, from its counters (the sum of their
-// copies) and base.  Run by the last workgroup of the level-0 launch.
+// copies) and base, and what a chained stack or the quadrant check makes of
+// them (a launch of its own takes about 4 us).  Run by the last workgroup of
+// the level-0 launch.
 __device__ void finalize_level0(const SearchArgs &a)
 {
     __shared__ uint32_t tot[kMaxStack * 9];
+    __shared__ int32_t fin[kMaxStack][2];  // shifts by output row
+    const bool post = a.out.chain_ref >= 0 || a.out.flag;
     for (int i = threadIdx.x; i < a.npairs * 9; i += blockDim.x) {
         const uint32_t *cnt = pair_counters(a, i / 9, 0, 0) + i % 9;
         uint32_t s = 0;
@@ -1401,7 +1421,30 @@ __device__ void finalize_level0(const SearchArgs &a)
         const int bx = (int32_t)load_shared((const uint32_t *)bases);
         const int by = (int32_t)load_shared((const uint32_t *)bases + 1);
         const int best = argmin9(c);
-        write_level(a, p, 0, c, bx + best % 3 - 1, by + best / 3 - 1);
+        const int sx = bx + best % 3 - 1, sy = by + best / 3 - 1;
+        write_level(a, p, 0, c, sx, sy);
+        if (post) {
+            fin[a.out.pair_image[p]][0] = sx;
+            fin[a.out.pair_image[p]][1] = sy;
+        }
+    }
+    if (!post)
+        return;
+    __syncthreads();
+    const SearchOutputs &o = a.out;
+    if (o.flag) {
+        if (threadIdx.x == 0)
+            o.flag[0] = quadrants_differ(fin, o.tol);
+    } else if (threadIdx.x < 2) {
+        // One lane walks each side of the chain.
+        const int step = threadIdx.x == 0 ? -1 : 1;
+        int x = 0, y = 0;
+        for (int i = o.chain_ref + step; i >= 0 && i < o.n_out; i += step) {
+            x += fin[i][0];
+            y += fin[i][1];
+            o.shifts[2 * i] = x;
+            o.shifts[2 * i + 1] = y;
+        }
     }
 }
 
@@ -2338,6 +2381,8 @@ __global__ __launch_bounds__(256) void k_apply(ApplyArgs a)
 // Translations compose by addition: the shift of image i against the
 // reference is its shift against its neighbour towards the reference plus
 // that neighbour's shift against the reference.  One lane walks each side.
+// For searches whose level 0 has no launch that sees every pair
+// (search_finalizes).
 struct ChainArgs {
     int32_t *shifts;
     int32_t n, ref;
@@ -2372,15 +2417,7 @@ __global__ void k_quadrant_flag(QuadFlagArgs a)
 {
     if (threadIdx.x != 0)
         return;
-    int32_t f = 0;
-    for (int i = 0; i < 4; ++i)
-        for (int j = i + 1; j < 4; ++j)
-            for (int c = 0; c < 2; ++c) {
-                const int32_t d = a.shifts[2 * i + c] - a.shifts[2 * j + c];
-                if (d > a.tol || -d > a.tol)
-                    f = 1;
-            }
-    a.flag[0] = f;
+    a.flag[0] = quadrants_differ((const int32_t(*)[2])a.shifts, a.tol);
 }
 
 }  // namespace
@@ -2619,6 +2656,11 @@ bool small_search_fits(const Geometry &g) { return 2 * (g.med_off - kAlign) <= k
 bool small_search_used(const Geometry &g, const LaunchTune *t)
 {
     return (!t || t->small != 0) && small_search_fits(g);
+}
+
+bool search_finalizes(const Geometry &g, int npairs, const LaunchTune *t)
+{
+    return npairs > 0 && !small_search_used(g, t) && coarse_levels_used(g, npairs, t) < g.L;
 }
 
 hipError_t launch_search(SearchArgs a, int cus, hipStream_t s, const LaunchTune *t)

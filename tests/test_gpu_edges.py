@@ -142,3 +142,33 @@ def test_fine_levels_one_word_a_lane(mtb, n, w, h, L):
         assert np.array_equal(r["shifts"].cpu().numpy(), want["shifts"])
         assert np.array_equal(r["errs"].cpu().numpy().astype(np.int64), want["errs"])
         assert np.array_equal(r["trace"].cpu().numpy(), got["trace"].cpu().numpy())
+
+
+# The quadrant flag and the chained sums are formed by the search's last
+# workgroup where one launch sees every pair's level 0, else by a launch of
+# their own: quadrants that share one launch set, that do not (odd sizes), and
+# that one workgroup searches; stacks with all levels searched exhaustively.
+@pytest.mark.parametrize("w,h,L,extra_shift", [(1600, 1200, 6, 0), (1600, 1200, 6, 9), (1601, 1203, 5, 9), (1600, 1201, 6, 0),
+                                               (400, 300, 4, 9), (1600, 1200, 3, 9)])
+def test_quadrant_flag_of_the_search(mtb, w, h, L, extra_shift):
+    base = synth.expose(synth.rect_field(w, h, 60, np.random.default_rng(w + h + extra_shift)), 0.0)
+    mov = synth.translate(base, 3, -2)
+    mov[:h // 2, w // 2:] = synth.translate(base, 3 + extra_shift, -2)[:h // 2, w // 2:]
+    for tol in (0, 1, 60):
+        want = oracle.align_quadrants(base, mov, L, tolerance=tol)
+        got = mtb.mtb_align_quadrants(_view(base, 0, 0), _view(mov, 0, 0), L, tolerance=tol)
+        torch.cuda.synchronize()
+        assert np.array_equal(got["shifts"].cpu().numpy(), want["shifts"])
+        assert np.array_equal(got["errs"].cpu().numpy().astype(np.int64), want["errs"])
+        assert int(got["flag"].cpu()[0]) == want["flag"]
+
+
+@pytest.mark.parametrize("n,w,h,L", [(5, 640, 480, 3), (5, 640, 480, 2), (2, 900, 700, 5), (7, 901, 703, 6)])
+@pytest.mark.parametrize("ref", [0, 1])
+def test_chained_sums_of_the_search(mtb, n, w, h, L, ref):
+    imgs, _, _ = synth.make_stack(w, h, n, 30, 800 + n + L, 5, sat_frac=0.05)
+    want = oracle.align_stack_chained(imgs, L, ref_index=ref, threads=4)
+    got = mtb.mtb_align_stack_chained([_view(im, 0, 0) for im in imgs], L, ref_index=ref)
+    torch.cuda.synchronize()
+    assert np.array_equal(got["shifts"].cpu().numpy(), want["shifts"])
+    assert np.array_equal(got["errs"].cpu().numpy().astype(np.int64), want["errs"])
