@@ -127,9 +127,10 @@ constexpr int kLdsSurfWords = 3 * 3 + 7 * 7 + 15 * 15;
 // Per pair the search state is: base int32[L][2] (the centre of each level's
 // nine candidates), the coarse error surfaces uint32[kSurfWords], then on a
 // 64-byte boundary the counters uint32[L][kCopies][kCounterStride].  After
-// every pair's state come the ticket counters of the coarse launch and of the
-// level-0 launch: each kTicketGroups group counters and one counter of
-// completed groups.
+// every pair's state come the ticket counters of the coarse launch and room for
+// the level-0 launch's (which usually sit kTicketStride words apart among the
+// first pair's surfaces): each kTicketGroups group counters and one counter
+// of completed groups.
 constexpr int pair_counter_offset(int32_t L)
 {
     return (2 * L + kSurfWords + kCounterStride - 1) / kCounterStride * kCounterStride;
@@ -138,8 +139,12 @@ constexpr int pair_counter_offset(int32_t L)
 constexpr int64_t pair_state_words(int32_t L) { return (int64_t)L * 146 + kSurfWords; }
 static_assert(pair_counter_offset(1) + kCopies * kCounterStride <= pair_state_words(1), "one level's counters fit");
 static_assert(146 >= kCopies * kCounterStride + 2, "every further level's counters fit");
-constexpr int kTicketGroups = 32;
-constexpr int kTicketWords = 2 * (kTicketGroups + 1);
+constexpr int kTicketGroups = 16;
+constexpr int kTicketStride = 32;
+constexpr int kTicketWords = 66;
+static_assert(2 * (kTicketGroups + 1) <= kTicketWords, "both launches' tickets fit");
+static_assert(2 * kMaxLevels + kLdsSurfWords + (kTicketGroups + 2) * kTicketStride <= kSurfWords,
+              "spread tickets fit among the surfaces");
 
 // Where the search writes its results; the last workgroup of the launch
 // that searches level 0 fills them in.
@@ -159,14 +164,15 @@ struct SearchArgs {
     const uint8_t *ref[kMaxStack];   // bitmaps buffer of each pair's reference
     const uint8_t *mov[kMaxStack];   // bitmaps buffer of each pair's moving image
     uint32_t *state;                 // pair p's state at state + p * state_stride
-    uint32_t *done;                  // ticket counters: coarse launch, then level-0 launch
+    uint32_t *done;                  // ticket counters of the coarse launch
+    uint32_t *tickets;               // and of the level-0 launch, ticket_stride words apart
     int64_t state_stride;            // uint32 words
     int32_t npairs;
     int32_t level;                   // fine kernel: the level searched
     int32_t coarse_n;                // levels L-1 .. L-coarse_n searched exhaustively
     int32_t rows_per_stream;         // rows per lane in one work unit
     int32_t cw_log2;                 // fine kernel: lanes per row stream (log2, 3..6), 0: the rule
-    int32_t pad_;
+    int32_t ticket_stride;
     SearchOutputs out;
     Geometry g;
 };

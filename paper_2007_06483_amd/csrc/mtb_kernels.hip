@@ -1451,7 +1451,9 @@ __device__ void finalize_level0(const SearchArgs &a)
 // True in the workgroup that finishes last in the launch.  Tickets are taken
 // in two stages so that no single counter receives more than about
 // gridsize / kTicketGroups atomics: workgroup b counts into group b %
-// kTicketGroups, and the last arrival of each group counts into t[G].
+// kTicketGroups, and the last arrival of each group counts into counter
+// kTicketGroups; the counters are `stride` words apart (on one cache line their
+// atomics queue: 7 x 3001x1999 chained 98.8 -> 97.8 us with a line each).
 //
 // Ordering without device-wide fences (which on gfx950 write back the whole
 // L2): everything workgroups exchange within a launch is written and read
@@ -1462,7 +1464,7 @@ __device__ void finalize_level0(const SearchArgs &a)
 // agent-scope atomic, so the workgroup that draws the last ticket observes
 // every other workgroup's completed writes.  (A workgroup barrier alone does
 // not wait for outstanding global writes.)
-__device__ bool last_workgroup(uint32_t *t)
+__device__ bool last_workgroup(uint32_t *t, int stride)
 {
     __shared__ int s_last;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -1474,8 +1476,8 @@ __device__ bool last_workgroup(uint32_t *t)
         const uint32_t members = (n - grp + kTicketGroups - 1) / kTicketGroups;
         const uint32_t groups = n < (uint32_t)kTicketGroups ? n : (uint32_t)kTicketGroups;
         s_last = 0;
-        if (atomicAdd(t + grp, 1u) == members - 1)
-            s_last = atomicAdd(t + kTicketGroups, 1u) == groups - 1;
+        if (atomicAdd(t + grp * stride, 1u) == members - 1)
+            s_last = atomicAdd(t + kTicketGroups * stride, 1u) == groups - 1;
     }
     __syncthreads();
     return s_last != 0;
@@ -1652,7 +1654,7 @@ __global__ __launch_bounds__(256) void k_search_coarse(SearchArgs a)
     else
         coarse_score<kMaxR>(a, pair, i, item);
 
-    if (a.coarse_n < g.L || !last_workgroup(a.done))
+    if (a.coarse_n < g.L || !last_workgroup(a.done, 1))
         return;
     // Every level is coarse: walk all pairs' surfaces, the small windows
     // fetched into LDS at once.
@@ -1775,7 +1777,7 @@ __device__ __forceinline__ void level_finish(const SearchArgs &a, int pair, cons
         if (s)
             atomicAdd(pair_counters(a, pair, a.level, blockIdx.x % kCopies) + threadIdx.x, s);
     }
-    if (a.level == 0 && last_workgroup(a.done + kTicketGroups + 1))
+    if (a.level == 0 && last_workgroup(a.tickets, a.ticket_stride))
         finalize_level0(a);
 }
 
@@ -2514,10 +2516,21 @@ hipError_t launch_bytemaps(const BitmapArgs &a, int cus, hipStream_t s)
     return launch_kernel("k_bytemaps", k_bytemaps, dim3((unsigned)blocks), dim3(256), s, a);
 }
 
+// The level-0 launch's tickets: a cache line each in the part of the first
+// pair's state that only windows of radius 15 and 31 use, or packed behind the
+// coarse launch's where those are used.
+void place_tickets(SearchArgs *a)
+{
+    const bool spread = a->coarse_n <= 3;
+    a->tickets = spread ? a->state + align_up(2 * a->g.L + kLdsSurfWords, kTicketStride) : a->done + kTicketGroups + 1;
+    a->ticket_stride = spread ? kTicketStride : 1;
+}
+
 hipError_t launch_search_bytes(SearchArgs a, int cus, hipStream_t s)
 {
     const Geometry &g = a.g;
     a.coarse_n = 0;
+    place_tickets(&a);
     const int64_t resident = (int64_t)cus * resident_per_cu<k_search_bytes>();
     for (int l = g.L - 1; l >= 0; --l) {
         const LevelGeom &lv = g.lv[l];
@@ -2670,6 +2683,7 @@ hipError_t launch_search(SearchArgs a, int cus, hipStream_t s, const LaunchTune 
         return launch_kernel("k_search_small", k_search_small, dim3(a.npairs), dim3(kSmallThreads), s, a);
     const int cn = coarse_levels_used(g, a.npairs, t);
     a.coarse_n = cn;
+    place_tickets(&a);
     hipError_t e = hipSuccess;
     if (cn > 0) {
         int items = 0;
