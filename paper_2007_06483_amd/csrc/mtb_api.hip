@@ -226,6 +226,14 @@ hipError_t enqueue_set(const PairSet &ps, const Geometry &g, int64_t stride, int
     ba.pairs = pairs;
     ba.g = g;
     fill_chunk_starts(g, ba.chunk_start, pairs);
+    ba.coarse_items = bytemaps ? 0 : coarse_items_in_bitmaps(g, npairs, cus, t);
+    ba.coarse_blocks = ba.coarse_items * npairs;
+    for (int p = 0; p < npairs; ++p) {
+        ba.ref_img[p] = (uint8_t)ps.ref_img[p];
+        ba.mov_img[p] = (uint8_t)ps.mov_img[p];
+    }
+    ba.state = state;
+    ba.state_stride = sstride;
     e = bytemaps ? launch_bytemaps(ba, cus, s) : launch_bitmaps(ba, cus, s, t.bm_pct, t.bm_waves);
     if (e != hipSuccess || npairs == 0)
         return e;
@@ -243,7 +251,7 @@ hipError_t enqueue_set(const PairSet &ps, const Geometry &g, int64_t stride, int
     sa.npairs = npairs;
     sa.out = out;
     sa.g = g;
-    return bytemaps ? launch_search_bytes(sa, cus, s) : launch_search(sa, cus, s, &t);
+    return bytemaps ? launch_search_bytes(sa, cus, s) : launch_search(sa, cus, s, &t, ba.coarse_blocks > 0);
 }
 
 // Tuned launch shapes, per (images, size, levels, row alignment); filled by

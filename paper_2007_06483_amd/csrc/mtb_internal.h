@@ -111,6 +111,12 @@ struct BitmapArgs {
     int32_t pad_;
     int64_t chunk_start[kMaxLevels + 1];  // first chunk (or unit) of each level within one image
     Geometry g;
+    // The coarse search in the same launch: its workgroups (0: none; they come
+    // first), items per pair, the pairs' images and search state.
+    int32_t coarse_blocks, coarse_items;
+    uint8_t ref_img[kMaxStack], mov_img[kMaxStack];
+    uint32_t *state;
+    int64_t state_stride;
 };
 
 // ------------------------------------------------------------------ search
@@ -285,7 +291,14 @@ bool small_search_used(const Geometry &g, const LaunchTune *t);
 // Whether one launch of the search sees every pair's level-0 result, so that
 // it can sum a chained stack's shifts or form the quadrant flag itself.
 bool search_finalizes(const Geometry &g, int npairs, const LaunchTune *t);
+// Items per pair of a coarse search that a bitmaps launch of shape t can take
+// along (BitmapArgs::coarse_blocks = items * npairs), 0 if it cannot: four
+// wavefronts a workgroup, one to three coarse levels with rows of at most 64
+// words, and a finer level below them that walks their surfaces.
+int coarse_items_in_bitmaps(const Geometry &g, int npairs, int device_cus, const LaunchTune &t);
 // t: the launch shape (rows and lanes per stream per level, coarse levels), or null for the rules.
-hipError_t launch_search(SearchArgs a, int device_cus, hipStream_t s, const LaunchTune *t = nullptr);
+// coarse_done: the bitmaps launch took the coarse levels along.
+hipError_t launch_search(SearchArgs a, int device_cus, hipStream_t s, const LaunchTune *t = nullptr,
+                         bool coarse_done = false);
 
 }  // namespace mtb

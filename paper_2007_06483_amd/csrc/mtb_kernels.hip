@@ -3,7 +3,8 @@
 // Pass 1  k_pyramid         RGB -> gray levels 0..6 of 64x256 tiles + LDS histograms
 //         k_pyramid_coarse  levels 7.. from level 6 (one workgroup per image)
 // Pass 2  k_bitmaps         gray -> lower median per level, packed T/E words
-// Search  k_search_coarse   small levels, one workgroup per pair, all in one launch
+// Search  k_search_coarse   small levels, exhaustive windows, all in one launch (or as
+//                           part of k_bitmaps)
 //         k_search_pos      one launch per finer level while a lane can take one word of it,
 //         k_search_fine     beyond that units of rows; grid over (workgroups, pairs);
 //                           the last workgroup of the level-0 launch writes the results
@@ -602,6 +603,97 @@ __device__ __forceinline__ uint32_t wave_median(const uint32_t *hist, uint32_t n
 }
 
 
+// ---------------------------------------------------------------- coarse windows, shared parts
+
+__device__ __forceinline__ uint32_t funnel(uint32_t hi, uint32_t lo, uint32_t sh)
+{
+    return __builtin_amdgcn_alignbit(hi, lo, sh);
+}
+
+// Sums each of v[0..N) over the wavefront (every lane gets the totals).
+// Within each row of 16 lanes, DPP moves (no LDS): swap neighbours, swap
+// pairs (quad permutes), mirror each half-row, mirror the row — after which
+// every lane holds its row's sum; the last two steps cross rows with
+// ds_bpermute, the N exchanges of a step all in flight at once.
+template <int N>
+__device__ __forceinline__ void wave_sums(uint32_t *v)
+{
+#pragma unroll
+    for (int i = 0; i < N; ++i)  // quad_perm [1,0,3,2]
+        v[i] += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v[i], 0xb1, 0xf, 0xf, true);
+#pragma unroll
+    for (int i = 0; i < N; ++i)  // quad_perm [2,3,0,1]
+        v[i] += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v[i], 0x4e, 0xf, 0xf, true);
+#pragma unroll
+    for (int i = 0; i < N; ++i)  // row_half_mirror
+        v[i] += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v[i], 0x141, 0xf, 0xf, true);
+#pragma unroll
+    for (int i = 0; i < N; ++i)  // row_mirror
+        v[i] += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v[i], 0x140, 0xf, 0xf, true);
+#pragma unroll
+    for (int d = 16; d <= 32; d <<= 1) {
+        uint32_t o[N];
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+            o[i] = __shfl_xor(v[i], d);
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+            v[i] += o[i];
+    }
+}
+
+// Radius of the exhaustive window at the i-th coarsest level, and where its
+// (2R+1)^2 surface starts.
+__host__ __device__ __forceinline__ int coarse_radius(int i) { return (2 << i) - 1; }
+__device__ __forceinline__ int coarse_surface_offset(int i)
+{
+    return i == 0 ? 0 : i == 1 ? 9 : i == 2 ? 58 : i == 3 ? 283 : 1244;
+}
+
+// Column width (log2, in dwords) and row slabs of a coarse level handled by
+// 256-lane workgroups: CW = 2^cw_log2 columns x 256 / CW row streams, each
+// stream scoring 8 rows of a slab.
+__host__ __device__ __forceinline__ int coarse_cw_log2(const LevelGeom &lv)
+{
+    int c = 0;
+    while ((1 << c) < 2 * lv.wpr && c < 6)
+        ++c;
+    return c;
+}
+
+// Rows per stream of one coarse workgroup (all its loads are issued first).
+// Four rather than eight: twice the workgroups, each with half the serial
+// work, and more of them per compute unit to hide each other's latency.
+constexpr int kCoarseRows = 4;
+
+__host__ __device__ __forceinline__ int coarse_slab_rows(const LevelGeom &lv)
+{
+    return kCoarseRows * (256 >> coarse_cw_log2(lv));
+}
+
+__host__ __device__ __forceinline__ int coarse_slabs(const LevelGeom &lv)
+{
+    const int rows = coarse_slab_rows(lv);
+    return (lv.h + rows - 1) / rows;
+}
+
+// Item `item` of a coarse launch (or of the coarse blocks of a bitmaps launch):
+// the i-th coarsest level and the item's place among that level's, which is
+// (window row, slab).
+__device__ __forceinline__ int coarse_item(const Geometry &g, int item, int *place)
+{
+    int i = 0;
+    for (;;) {
+        const int cnt = (2 * coarse_radius(i) + 1) * coarse_slabs(g.lv[g.L - 1 - i]);
+        if (item < cnt)
+            break;
+        item -= cnt;
+        ++i;
+    }
+    *place = item;
+    return i;
+}
+
 struct ChunkPos {
     int img, level, w0, cnt;
 };
@@ -752,6 +844,22 @@ __device__ __forceinline__ void te_bits_of(const uint32_t *d, const Thresholds &
         tw = (ta[0] + (ta[1] << 8)) >> 7;
         ew = ~((ba[0] + (ba[1] << 8)) >> 7);
     }
+}
+
+// Eight dwords' T and E bits with the cases picked at run time.
+__device__ __forceinline__ void te_bits_any(const uint32_t *d, const Thresholds &c, uint32_t &tw, uint32_t &ew)
+{
+    uint32_t ta[4], ba[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        uint32_t t0, t1, b0, b1;
+        te_marks_any(d[2 * k], c, t0, b0);
+        te_marks_any(d[2 * k + 1], c, t1, b1);
+        ta[k] = mark_bits8(t0, t1);
+        ba[k] = mark_bits8(b0, b1);
+    }
+    tw = ((ta[0] + (ta[1] << 8) + (ta[2] << 16)) >> 7) | (ta[3] << 17);
+    ew = ~(((ba[0] + (ba[1] << 8) + (ba[2] << 16)) >> 7) | (ba[3] << 17));
 }
 
 template <int kDwords>
@@ -961,22 +1069,134 @@ __device__ __forceinline__ void walk_units(const BitmapArgs &a, int64_t c0, int6
     }
 }
 
+// Coarse item of a pair (see k_search_coarse: the errors of one row of a level's
+// window over one slab, added into the pair's error surface) from the gray
+// levels instead of the bitmaps, so that it can run in the launch that writes
+// the bitmaps: a lane forms its reference and moving words from 32 pixels
+// each, and takes the moving words either side from its neighbours.  256
+// threads; rows of at most 64 words.
+__device__ __forceinline__ void coarse_from_gray(const BitmapArgs &a, int pair, int item)
+{
+    constexpr int kMaxR = 7, kBatch = 2;
+    __shared__ uint32_t red[4][2 * kMaxR + 1];
+    const int wave = wave_id();
+    const int lane = threadIdx.x & 63;
+    const Geometry &g = a.g;
+    int place;
+    const int i = coarse_item(g, item, &place);
+    const int l = g.L - 1 - i;
+    const LevelGeom &lv = g.lv[l];
+    const int R = coarse_radius(i), slabs = coarse_slabs(lv);
+    const int cy = place / slabs - R, y_lo = place % slabs * coarse_slab_rows(lv);
+    const int n32 = 2 * lv.wpr, h = lv.h;
+    const uint8_t *ref = a.pyr[a.ref_img[pair]], *mov = a.pyr[a.mov_img[pair]];
+    const uint32_t npix = (uint32_t)(lv.w * lv.h), X = (uint32_t)a.exclude;
+    const uint4 hr = wave_hist((const uint32_t *)(ref + g.hist_off) + 256 * l);
+    const uint4 hm = wave_hist((const uint32_t *)(mov + g.hist_off) + 256 * l);
+    const Thresholds tr = thresholds(wave_median_of(hr, npix), X), tm = thresholds(wave_median_of(hm, npix), X);
+
+    const int cw_log2 = coarse_cw_log2(lv);
+    const int streams = 256 >> cw_log2;
+    const int k = threadIdx.x & ((1 << cw_log2) - 1), stream = threadIdx.x >> cw_log2;
+    // Pixels past the level's width have no defined value: their E bits are cleared.
+    const int nb = lv.w - 32 * k;
+    const uint32_t keep = nb >= 32 ? ~0u : (nb <= 0 ? 0u : (1u << nb) - 1u);
+    const uint32_t cm0 = k >= 1 ? ~0u : 0u, cm2 = k + 1 < n32 ? ~0u : 0u;
+    const int64_t col = 32 * (int64_t)(k < n32 ? k : n32 - 1);
+    ref += lv.gray_off + col;
+    mov += lv.gray_off + col;
+
+    uint32_t acc[2 * kMaxR + 1];
+#pragma unroll
+    for (int c = 0; c < 2 * kMaxR + 1; ++c)
+        acc[c] = 0u;
+#pragma unroll 1
+    for (int b0 = 0; b0 < kCoarseRows; b0 += kBatch) {
+        uint4 vr[kBatch][2], vm[kBatch][2];
+#pragma unroll
+        for (int b = 0; b < kBatch; ++b) {
+            const int y = y_lo + stream + (b0 + b) * streams, j = y - cy;
+            const uint4 *pr = (const uint4 *)(ref + (y < h ? y : h - 1) * lv.gray_pitch);
+            const uint4 *pm = (const uint4 *)(mov + (j < 0 ? 0 : (j >= h ? h - 1 : j)) * lv.gray_pitch);
+            vr[b][0] = pr[0];
+            vr[b][1] = pr[1];
+            vm[b][0] = pm[0];
+            vm[b][1] = pm[1];
+        }
+#pragma unroll
+        for (int b = 0; b < kBatch; ++b) {
+            const int y = y_lo + stream + (b0 + b) * streams;
+            const uint32_t dr[8] = {vr[b][0].x, vr[b][0].y, vr[b][0].z, vr[b][0].w,
+                                    vr[b][1].x, vr[b][1].y, vr[b][1].z, vr[b][1].w};
+            const uint32_t dm[8] = {vm[b][0].x, vm[b][0].y, vm[b][0].z, vm[b][0].w,
+                                    vm[b][1].x, vm[b][1].y, vm[b][1].z, vm[b][1].w};
+            uint32_t t, e, t1, e1;
+            te_bits_any(dr, tr, t, e);
+            te_bits_any(dm, tm, t1, e1);
+            e = y < h ? e & keep : 0u;
+            e1 = (uint32_t)(y - cy) < (uint32_t)h ? e1 & keep : 0u;
+            const uint32_t t0 = __shfl_up(t1, 1), t2 = __shfl_down(t1, 1);
+            const uint32_t e0 = __shfl_up(e1, 1) & cm0, e2 = __shfl_down(e1, 1) & cm2;
+#pragma unroll
+            for (int c = 0; c < 2 * kMaxR + 1; ++c) {
+                const int cx = c - kMaxR;
+                if (cx >= -R && cx <= R) {
+                    const int o = 32 - cx;  // bit offset from the start of word k-1
+                    const uint32_t st = o < 32 ? funnel(t1, t0, o) : funnel(t2, t1, o - 32);
+                    const uint32_t se = o < 32 ? funnel(e1, e0, o) : funnel(e2, e1, o - 32);
+                    acc[c] += __builtin_popcount((t ^ st) & e & se);
+                }
+            }
+        }
+    }
+    wave_sums<2 * kMaxR + 1>(acc);
+    if (lane == 0)
+#pragma unroll
+        for (int c = 0; c < 2 * kMaxR + 1; ++c)
+            red[wave][c] = acc[c];
+    __syncthreads();
+    if ((int)threadIdx.x < 2 * R + 1) {
+        const int c = threadIdx.x + kMaxR - R;
+        const uint32_t v = red[0][c] + red[1][c] + red[2][c] + red[3][c];
+        if (v)
+            atomicAdd(a.state + pair * a.state_stride + 2 * g.L + coarse_surface_offset(i) + (cy + R) * (2 * R + 1) +
+                          threadIdx.x,
+                      v);
+    }
+}
+
 // The bitmaps pass.  Bound by HBM: 7 x 6000x4000 takes 54 us for 238 MB (4.4
 // TB/s; the plain 4:1 stream reaches 5.35; 57 us before the dot products and
 // the shorter runs), 9 x 8485x5657 129 us for 612 MB (151).  Without kPairs every
 // level is walked in chunks.  With
 // kPairs (a.pairs; at least two levels) the launch's items are first every
 // image's pair units, which yield levels 0 and 1, then every image's chunks
-// of levels 2 .. L-1; a wavefront takes a contiguous run of items.
-template <int kW, bool kPairs>
-__global__ __launch_bounds__(64 * kW) __attribute__((amdgpu_waves_per_eu(kPairs ? 6 : 1))) void k_bitmaps(BitmapArgs a)
+// of levels 2 .. L-1; a wavefront takes a contiguous run of items.  The first
+// a.coarse_blocks workgroups (with kCoarse) are the coarse search's: it needs
+// only the smallest gray levels, its chain is as long as a launch (5.6 to 7 us
+// behind this one), and here the other workgroups' stream hides part of it:
+// 4096x3072 pair 64.3 -> 60.6 us, quadrants of 6000x4000 102 -> 97, 7 x
+// 6000x4000 237 -> 234.5.  The coarse blocks' registers hold the launch to
+// seven wavefronts a SIMD (six with kPairs): prefetching their rows, at more
+// registers, was 1 us slower on the pair.
+template <int kW, bool kPairs, bool kCoarse>
+__global__ __launch_bounds__(64 * kW) __attribute__((amdgpu_waves_per_eu(kPairs ? 6 : (kCoarse ? 7 : 1)))) void k_bitmaps(
+    BitmapArgs a)
 {
     const int wave = wave_id();
     const int lane = threadIdx.x & 63;
     const int64_t per_image = a.chunk_start[a.g.L];
     const int64_t total = per_image * a.n;
-    const int64_t nwaves = (int64_t)gridDim.x * kW;
-    const int64_t gw = (int64_t)blockIdx.x * kW + wave;
+    const int coarse = kCoarse ? a.coarse_blocks : 0;
+    if constexpr (kCoarse) {
+        static_assert(kW == 4, "coarse items take 256 threads");
+        if ((int)blockIdx.x < coarse) {
+            coarse_from_gray(a, blockIdx.x / a.coarse_items, blockIdx.x % a.coarse_items);
+            return;
+        }
+    }
+    const int64_t nwaves = (int64_t)(gridDim.x - coarse) * kW;
+    const int64_t gw = (int64_t)(blockIdx.x - coarse) * kW + wave;
     const int64_t per_wave = (total + nwaves - 1) / nwaves;
     const int64_t c0 = gw * per_wave;
     const int64_t c1 = c0 + per_wave < total ? c0 + per_wave : total;
@@ -1067,11 +1287,6 @@ __global__ __launch_bounds__(256) void k_bytemaps(BitmapArgs a)
 }
 
 // ---------------------------------------------------------------- search
-
-__device__ __forceinline__ uint32_t funnel(uint32_t hi, uint32_t lo, uint32_t sh)
-{
-    return __builtin_amdgcn_alignbit(hi, lo, sh);
-}
 
 // One batch of kB reference rows of a work unit and, for each, the moving row
 // one below it (ddy = -1): the lane's two reference words and kW words of the
@@ -1291,38 +1506,6 @@ __device__ __forceinline__ void search_unit(const uint8_t *ref, const uint8_t *m
         search_unit_t<2>(ref, mov, lv, bx, by, unit, cw_log2, rows, units_x, acc);
 }
 
-// Sums each of v[0..N) over the wavefront (every lane gets the totals).
-// Within each row of 16 lanes, DPP moves (no LDS): swap neighbours, swap
-// pairs (quad permutes), mirror each half-row, mirror the row — after which
-// every lane holds its row's sum; the last two steps cross rows with
-// ds_bpermute, the N exchanges of a step all in flight at once.
-template <int N>
-__device__ __forceinline__ void wave_sums(uint32_t *v)
-{
-#pragma unroll
-    for (int i = 0; i < N; ++i)  // quad_perm [1,0,3,2]
-        v[i] += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v[i], 0xb1, 0xf, 0xf, true);
-#pragma unroll
-    for (int i = 0; i < N; ++i)  // quad_perm [2,3,0,1]
-        v[i] += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v[i], 0x4e, 0xf, 0xf, true);
-#pragma unroll
-    for (int i = 0; i < N; ++i)  // row_half_mirror
-        v[i] += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v[i], 0x141, 0xf, 0xf, true);
-#pragma unroll
-    for (int i = 0; i < N; ++i)  // row_mirror
-        v[i] += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v[i], 0x140, 0xf, 0xf, true);
-#pragma unroll
-    for (int d = 16; d <= 32; d <<= 1) {
-        uint32_t o[N];
-#pragma unroll
-        for (int i = 0; i < N; ++i)
-            o[i] = __shfl_xor(v[i], d);
-#pragma unroll
-        for (int i = 0; i < N; ++i)
-            v[i] += o[i];
-    }
-}
-
 // First minimum in ddy-major order; returns the candidate index 0..8.
 __device__ __forceinline__ int argmin9(const uint32_t *c)
 {
@@ -1350,14 +1533,6 @@ __device__ __forceinline__ uint32_t *pair_surface(const SearchArgs &a, int p)
 __device__ __forceinline__ uint32_t *pair_counters(const SearchArgs &a, int p, int l, int c)
 {
     return pair_state(a, p) + pair_counter_offset(a.g.L) + (l * kCopies + c) * kCounterStride;
-}
-
-// Radius of the exhaustive window at the i-th coarsest level, and where its
-// (2R+1)^2 surface starts.
-__host__ __device__ __forceinline__ int coarse_radius(int i) { return (2 << i) - 1; }
-__device__ __forceinline__ int coarse_surface_offset(int i)
-{
-    return i == 0 ? 0 : i == 1 ? 9 : i == 2 ? 58 : i == 3 ? 283 : 1244;
 }
 
 // Records level l's nine errors and chosen shift in pair p's output row.
@@ -1481,33 +1656,6 @@ __device__ bool last_workgroup(uint32_t *t, int stride)
     }
     __syncthreads();
     return s_last != 0;
-}
-
-// Column width (log2, in dwords) and row slabs of a coarse level handled by
-// 256-lane workgroups: CW = 2^cw_log2 columns x 256 / CW row streams, each
-// stream scoring 8 rows of a slab.
-__host__ __device__ __forceinline__ int coarse_cw_log2(const LevelGeom &lv)
-{
-    int c = 0;
-    while ((1 << c) < 2 * lv.wpr && c < 6)
-        ++c;
-    return c;
-}
-
-// Rows per stream of one coarse workgroup (all its loads are issued first).
-// Four rather than eight: twice the workgroups, each with half the serial
-// work, and more of them per compute unit to hide each other's latency.
-constexpr int kCoarseRows = 4;
-
-__host__ __device__ __forceinline__ int coarse_slab_rows(const LevelGeom &lv)
-{
-    return kCoarseRows * (256 >> coarse_cw_log2(lv));
-}
-
-__host__ __device__ __forceinline__ int coarse_slabs(const LevelGeom &lv)
-{
-    const int rows = coarse_slab_rows(lv);
-    return (lv.h + rows - 1) / rows;
 }
 
 // Walks pair p's coarse error surfaces from the coarsest level down, testing
@@ -1641,14 +1789,8 @@ __global__ __launch_bounds__(256) void k_search_coarse(SearchArgs a)
 {
     const int pair = blockIdx.y;
     const Geometry &g = a.g;
-    int item = blockIdx.x, i = 0;
-    for (;;) {
-        const int cnt = (2 * coarse_radius(i) + 1) * coarse_slabs(g.lv[g.L - 1 - i]);
-        if (item < cnt)
-            break;
-        item -= cnt;
-        ++i;
-    }
+    int item;
+    const int i = coarse_item(g, blockIdx.x, &item);
     if (kMaxR == 7 || coarse_radius(i) <= 7)
         coarse_score<7>(a, pair, i, item);
     else
@@ -2560,16 +2702,16 @@ hipError_t launch_search_bytes(SearchArgs a, int cus, hipStream_t s)
 // 2.3 items each made 7 x 3001x1999 1 us slower.
 constexpr int kItemsPerWave = 4;
 
-template <int kW, bool kPairs>
+template <int kW, bool kPairs, bool kCoarse = false>
 hipError_t launch_bitmaps_w(const BitmapArgs &a, int cus, hipStream_t s, int blocks_pct)
 {
     const int64_t total = a.chunk_start[a.g.L] * a.n;
     int64_t blocks = (total + kW - 1) / kW;
-    const int64_t round = (int64_t)cus * resident_per_cu<k_bitmaps<kW, kPairs>, 64 * kW>();
+    const int64_t round = (int64_t)cus * resident_per_cu<k_bitmaps<kW, kPairs, kCoarse>, 64 * kW>();
     const int64_t most = total / (kW * kItemsPerWave);
     const int64_t cap = (most > round ? most : round) * blocks_pct / 100;
-    blocks = blocks > cap ? cap : (blocks < 1 ? 1 : blocks);
-    return launch_kernel("k_bitmaps", k_bitmaps<kW, kPairs>, dim3((unsigned)blocks), dim3(64 * kW), s, a);
+    blocks = (blocks > cap ? cap : (blocks < 1 ? 1 : blocks)) + a.coarse_blocks;
+    return launch_kernel("k_bitmaps", k_bitmaps<kW, kPairs, kCoarse>, dim3((unsigned)blocks), dim3(64 * kW), s, a);
 }
 
 template <bool kPairs>
@@ -2577,6 +2719,8 @@ hipError_t launch_bitmaps_p(const BitmapArgs &a, int cus, hipStream_t s, int blo
 {
     // Wavefronts walk their items independently; the workgroup size only
     // changes how the launch is cut (a launch-shape knob).
+    if (a.coarse_blocks > 0)
+        return launch_bitmaps_w<4, kPairs, true>(a, cus, s, blocks_pct);
     if (waves == 2)
         return launch_bitmaps_w<2, kPairs>(a, cus, s, blocks_pct);
     if (waves == 8)
@@ -2676,7 +2820,33 @@ bool search_finalizes(const Geometry &g, int npairs, const LaunchTune *t)
     return npairs > 0 && !small_search_used(g, t) && coarse_levels_used(g, npairs, t) < g.L;
 }
 
-hipError_t launch_search(SearchArgs a, int cus, hipStream_t s, const LaunchTune *t)
+// Items of a coarse launch per pair.
+int coarse_item_count(const Geometry &g, int cn)
+{
+    int items = 0;
+    for (int i = 0; i < cn; ++i)
+        items += (2 * coarse_radius(i) + 1) * coarse_slabs(g.lv[g.L - 1 - i]);
+    return items;
+}
+
+// More coarse workgroups than this a compute unit are a launch of their own: 9 x
+// 8485x5657 has 1632, and taking them along made it 7 us slower; the 420 of 7 x
+// 6000x4000 still pay.
+constexpr int kCoarseBlocksPerCu = 2;
+
+int coarse_items_in_bitmaps(const Geometry &g, int npairs, int cus, const LaunchTune &t)
+{
+    const int cn = coarse_levels_used(g, npairs, &t);
+    if (npairs < 1 || small_search_used(g, &t) || t.bm_waves != 4 || cn < 1 || cn > 3 || cn >= g.L)
+        return 0;
+    for (int i = 0; i < cn; ++i)
+        if (2 * g.lv[g.L - 1 - i].wpr > kWave)
+            return 0;
+    const int items = coarse_item_count(g, cn);
+    return (int64_t)items * npairs <= (int64_t)kCoarseBlocksPerCu * cus ? items : 0;
+}
+
+hipError_t launch_search(SearchArgs a, int cus, hipStream_t s, const LaunchTune *t, bool coarse_done)
 {
     const Geometry &g = a.g;
     if (small_search_used(g, t))
@@ -2685,12 +2855,9 @@ hipError_t launch_search(SearchArgs a, int cus, hipStream_t s, const LaunchTune 
     a.coarse_n = cn;
     place_tickets(&a);
     hipError_t e = hipSuccess;
-    if (cn > 0) {
-        int items = 0;
-        for (int i = 0; i < cn; ++i)
-            items += (2 * coarse_radius(i) + 1) * coarse_slabs(g.lv[g.L - 1 - i]);
-        e = launch_kernel("k_search_coarse", cn > 3 ? k_search_coarse<31> : k_search_coarse<7>, dim3(items, a.npairs),
-                          dim3(256), s, a);
+    if (cn > 0 && !coarse_done) {
+        e = launch_kernel("k_search_coarse", cn > 3 ? k_search_coarse<31> : k_search_coarse<7>,
+                          dim3(coarse_item_count(g, cn), a.npairs), dim3(256), s, a);
         if (e != hipSuccess)
             return e;
     }

@@ -172,3 +172,32 @@ def test_chained_sums_of_the_search(mtb, n, w, h, L, ref):
     torch.cuda.synchronize()
     assert np.array_equal(got["shifts"].cpu().numpy(), want["shifts"])
     assert np.array_equal(got["errs"].cpu().numpy().astype(np.int64), want["errs"])
+
+
+# The coarse levels are searched from the gray levels inside the bitmaps launch
+# while their rows hold at most 64 words and their workgroups are few, else by
+# a launch of their own: sizes on both sides, level widths that end inside a
+# word (the gray behind them is whatever the workspace held), every number of
+# coarse levels, one to many slabs.
+@pytest.mark.parametrize("n,w,h,L,coarse", [(3, 1000, 700, 5, -1), (3, 1000, 700, 5, 1), (3, 1000, 700, 5, 2),
+                                            (2, 1200, 3900, 6, -1), (2, 2301, 1700, 6, -1), (2, 3990, 531, 4, -1),
+                                            (2, 9000, 90, 4, -1), (2, 2040, 1031, 4, 3), (32, 1200, 900, 6, -1),
+                                            (2, 700, 1500, 10, -1), (3, 1000, 700, 5, 4), (2, 640, 480, 3, -1)])
+def test_coarse_levels_inside_the_bitmaps_launch(mtb, n, w, h, L, coarse):
+    imgs, _, _ = synth.make_stack(w, h, n, 12, 300 + w + L, min(1 << (min(L, 6) - 1), h // 8), sat_frac=0.05)
+    d = [_view(im, 0, 0) for im in imgs]
+    ws = torch.full((mtb.mtb_stack_workspace_bytes(n, w, h, L),), 173, dtype=torch.uint8, device=DEV)
+    mtb.mtb_tune_reset()
+    if coarse >= 0:
+        mtb.mtb_set_shape(n, w, h, 3 * w, L, {"coarse_levels": coarse, "small_search": 0})
+    try:
+        got = mtb.mtb_align_stack(d, L, workspace=ws, trace=True)
+        mtb.mtb_set_shape(n, w, h, 3 * w, L, {"coarse_levels": 0, "small_search": 0})
+        alt = mtb.mtb_align_stack(d, L, trace=True)
+    finally:
+        mtb.mtb_tune_reset()
+    torch.cuda.synchronize()
+    want = oracle.align_stack(imgs, L, threads=4, keep=False)
+    assert np.array_equal(got["shifts"].cpu().numpy(), want["shifts"])
+    assert np.array_equal(got["errs"].cpu().numpy().astype(np.int64), want["errs"])
+    assert np.array_equal(got["trace"].cpu().numpy(), alt["trace"].cpu().numpy())
