@@ -2604,13 +2604,13 @@ hipError_t launch_pyramid(const PyramidArgs &in, int cus, hipStream_t s, int slo
     PyramidArgs a = in;
     a.tiles_x = (a.g.W + kTileW - 1) / kTileW;
     a.tiles_y = (a.g.H + kTileH - 1) / kTileH;
-    a.group_log2 = group_log2;
     const int64_t total = (int64_t)a.tiles_x * a.tiles_y * a.n;
     // One round of resident workgroups (scaled by slots_pct); each XCD gets
     // the same number of slots (see k_pyramid), at most one per tile group.
     const int64_t share = (total + kXcds - 1) / kXcds;
-    const int64_t groups = (share + (1 << group_log2) - 1) >> group_log2;
     int64_t slots = (int64_t)cus * resident_per_cu<k_pyramid>() * slots_pct / (100 * kXcds);
+    a.group_log2 = group_log2;
+    const int64_t groups = (share + (1 << group_log2) - 1) >> group_log2;
     slots = slots > groups ? groups : (slots < 1 ? 1 : slots);
     a.xcd_tiles = (int32_t)share;
     const int blocks = (int)(slots * kXcds);
@@ -2734,21 +2734,27 @@ hipError_t launch_bitmaps(const BitmapArgs &a, int cus, hipStream_t s, int block
                    : launch_bitmaps_p<false>(a, cus, s, blocks_pct, waves);
 }
 
-// The built-in rule searches the i-th coarsest level exhaustively when i < 3
-// and its window rows stay cheap for one workgroup: at most kCoarseDwords
-// dwords.  The windows of radius 15 and 31 (i = 3, 4) are taken only when a
+// The built-in rule searches the i-th coarsest level exhaustively when i < 3,
+// its window rows stay cheap for one workgroup (at most kCoarseDwords dwords)
+// and its whole window over every pair is worth the launch it saves (at most
+// kCoarseCells dwords times shifts: 9 x 8485x5657, 12.7 Mi at its third level,
+// 601 us a call with it and 593 without; 7 x 6000x4000, 3.9 Mi, 234 and 236).  The windows of radius 15 and 31 (i = 3, 4) are taken only when a
 // launch shape asks for them: on a mix of small stacks they cost more than
 // the fine launches they replace, and pairs small enough to gain from them
 // are searched by one workgroup instead.
 constexpr int64_t kCoarseDwords = 8192;
 constexpr int kCoarseRule = 3;
+constexpr int64_t kCoarseCells = 8 << 20;
 
 int coarse_level_count(const Geometry &g, int npairs)
 {
-    (void)npairs;
     int cn = 0;
-    while (cn < kCoarseRule && cn < g.L && (int64_t)2 * g.lv[g.L - 1 - cn].wpr * g.lv[g.L - 1 - cn].h <= kCoarseDwords)
-        ++cn;
+    for (; cn < kCoarseRule && cn < g.L; ++cn) {
+        const int64_t dwords = (int64_t)2 * g.lv[g.L - 1 - cn].wpr * g.lv[g.L - 1 - cn].h;
+        const int64_t side = 2 * coarse_radius(cn) + 1;
+        if (dwords > kCoarseDwords || dwords * side * side * npairs > kCoarseCells)
+            break;
+    }
     return cn;
 }
 

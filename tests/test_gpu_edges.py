@@ -182,6 +182,7 @@ def test_chained_sums_of_the_search(mtb, n, w, h, L, ref):
 @pytest.mark.parametrize("n,w,h,L,coarse", [(3, 1000, 700, 5, -1), (3, 1000, 700, 5, 1), (3, 1000, 700, 5, 2),
                                             (2, 1200, 3900, 6, -1), (2, 2301, 1700, 6, -1), (2, 3990, 531, 4, -1),
                                             (2, 9000, 90, 4, -1), (2, 2040, 1031, 4, 3), (32, 1200, 900, 6, -1),
+                                            (32, 2000, 1500, 6, -1),
                                             (2, 700, 1500, 10, -1), (3, 1000, 700, 5, 4), (2, 640, 480, 3, -1)])
 def test_coarse_levels_inside_the_bitmaps_launch(mtb, n, w, h, L, coarse):
     imgs, _, _ = synth.make_stack(w, h, n, 12, 300 + w + L, min(1 << (min(L, 6) - 1), h // 8), sat_frac=0.05)
