@@ -310,7 +310,7 @@ mtb_status mtb_align_stack_chained(const uint8_t *const *h_d_rgb, int32_t n, int
  */
 typedef struct mtb_launch_shape {
     int32_t pyramid_slots_pct;  /* 25 .. 400 (default 100) */
-    int32_t pyramid_tile_group; /* 1, 2 or 4 (default 1) */
+    int32_t pyramid_tile_group; /* 1, 2 or 4 (default 1: two where that gives each slot one group) */
     int32_t bitmaps_blocks_pct; /* 25 .. 100 (default 100) */
     int32_t bitmaps_waves;      /* 2, 4 or 8 (default 4) */
     int32_t coarse_levels;      /* -1 (rule), 0 .. 5 */

@@ -89,10 +89,12 @@ def test_apply_rows_at_every_alignment(mtb, w, extra, offset, out_extra, out_off
 
 
 # Beyond two tiles a workgroup, k_pyramid's workgroups claim tiles (in groups of
-# 1, 2 or 4 by launch shape); every tile must be counted exactly once, merged
+# 1, 2 or 4 by launch shape, or 2 by rule between one and two tiles a slot); every
+# tile must be counted exactly once, merged
 # histograms or not, also where every pixel falls into one bin.
 @pytest.mark.parametrize("n,w,h,pct,group", [(3, 4096, 3072, 25, 4), (3, 4096, 3072, 25, 2), (3, 4096, 3072, 25, 1),
-                                             (2, 4001, 3003, 25, 1), (1, 6000, 4200, 100, 1), (5, 3000, 2000, 50, 2)])
+                                             (2, 4001, 3003, 25, 1), (1, 6000, 4200, 100, 1), (5, 3000, 2000, 50, 2),
+                                             (3, 3000, 2000, 100, 1), (5, 2449, 1633, 100, 1), (4, 2560, 1440, 50, 1)])
 def test_pyramid_claimed_tiles(mtb, n, w, h, pct, group):
     L = 7
     rng = np.random.default_rng(w + n)
