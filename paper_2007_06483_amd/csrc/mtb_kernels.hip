@@ -150,8 +150,8 @@ __device__ __forceinline__ void fill_rgb16(int nb, uint32_t (&q)[4][12])
     }
 }
 
-// Tiles whose levels 5 and 6 wait in an LDS ring; the ring is drained by the
-// whole workgroup after one barrier, instead of one barrier per tile.
+// Tiles whose levels 5 and 6 wait in an LDS ring, which is drained by the whole
+// workgroup at once: a tile alone has 20 such pixels.
 constexpr int kDefer = 8;
 
 // Workgroup tile: kTileH = 64 rows x kTileW = 256 columns of level 0.  Wave w
