@@ -2705,7 +2705,8 @@ hipError_t launch_search_bytes(SearchArgs a, int cus, hipStream_t s)
 // on one front of addresses and even out the compute units; a wavefront's
 // start (two median scans) costs about an item.  With one round whatever the
 // size, 9 x 8485x5657 (45 items) took 23 us longer and 7 x 6000x4000 (14) 2-3;
-// 2.3 items each made 7 x 3001x1999 1 us slower.
+// 2.3 items each made 7 x 3001x1999 1 us slower, and three each 7 x 6000x4000
+// 2 us faster and quadrants of 6000x4000 2 us slower.
 constexpr int kItemsPerWave = 4;
 
 template <int kW, bool kPairs, bool kCoarse = false>
@@ -2744,10 +2745,11 @@ hipError_t launch_bitmaps(const BitmapArgs &a, int cus, hipStream_t s, int block
 // its window rows stay cheap for one workgroup (at most kCoarseDwords dwords)
 // and its whole window over every pair is worth the launch it saves (at most
 // kCoarseCells dwords times shifts: 9 x 8485x5657, 12.7 Mi at its third level,
-// 601 us a call with it and 593 without; 7 x 6000x4000, 3.9 Mi, 234 and 236).  The windows of radius 15 and 31 (i = 3, 4) are taken only when a
-// launch shape asks for them: on a mix of small stacks they cost more than
-// the fine launches they replace, and pairs small enough to gain from them
-// are searched by one workgroup instead.
+// 601 us a call with it and 593 without; 7 x 6000x4000, 3.9 Mi, 234 and 236).
+// The windows of radius 15 and 31 (i = 3, 4) are taken only when a launch
+// shape asks for them: on a mix of small stacks they cost more than the fine
+// launches they replace, and pairs small enough to gain from them are searched
+// by one workgroup instead.
 constexpr int64_t kCoarseDwords = 8192;
 constexpr int kCoarseRule = 3;
 constexpr int64_t kCoarseCells = 8 << 20;
