@@ -226,7 +226,7 @@ hipError_t enqueue_set(const PairSet &ps, const Geometry &g, int64_t stride, int
     ba.pairs = pairs;
     ba.g = g;
     fill_chunk_starts(g, ba.chunk_start, pairs);
-    ba.coarse_items = bytemaps ? 0 : coarse_items_in_bitmaps(g, npairs, cus, t);
+    ba.coarse_items = bytemaps ? 0 : coarse_items_in_bitmaps(g, npairs, cus, t, pairs);
     ba.coarse_blocks = ba.coarse_items * npairs;
     for (int p = 0; p < npairs; ++p) {
         ba.ref_img[p] = (uint8_t)ps.ref_img[p];

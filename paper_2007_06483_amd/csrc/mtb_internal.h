@@ -294,8 +294,10 @@ bool search_finalizes(const Geometry &g, int npairs, const LaunchTune *t);
 // Items per pair of a coarse search that a bitmaps launch of shape t can take
 // along (BitmapArgs::coarse_blocks = items * npairs), 0 if it cannot: four
 // wavefronts a workgroup, one to three coarse levels with rows of at most 64
-// words, and a finer level below them that walks their surfaces.
-int coarse_items_in_bitmaps(const Geometry &g, int npairs, int device_cus, const LaunchTune &t);
+// words, and a finer level below them that walks their surfaces.  It reads the
+// coarse levels' gray: with skip_l1 (PyramidArgs) level 1 must not be one of
+// them; the coarse launch, which reads the bitmaps, takes such a set.
+int coarse_items_in_bitmaps(const Geometry &g, int npairs, int device_cus, const LaunchTune &t, bool skip_l1);
 // t: the launch shape (rows and lanes per stream per level, coarse levels), or null for the rules.
 // coarse_done: the bitmaps launch took the coarse levels along.
 hipError_t launch_search(SearchArgs a, int device_cus, hipStream_t s, const LaunchTune *t = nullptr,

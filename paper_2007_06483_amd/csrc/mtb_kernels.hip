@@ -1074,7 +1074,7 @@ __device__ __forceinline__ void walk_units(const BitmapArgs &a, int64_t c0, int6
 // levels instead of the bitmaps, so that it can run in the launch that writes
 // the bitmaps: a lane forms its reference and moving words from 32 pixels
 // each, and takes the moving words either side from its neighbours.  256
-// threads; rows of at most 64 words.
+// threads; rows of at most 64 words; the level's gray must be stored.
 __device__ __forceinline__ void coarse_from_gray(const BitmapArgs &a, int pair, int item)
 {
     constexpr int kMaxR = 7, kBatch = 2;
@@ -2848,10 +2848,12 @@ int coarse_item_count(const Geometry &g, int cn)
 // 6000x4000 still pay.
 constexpr int kCoarseBlocksPerCu = 2;
 
-int coarse_items_in_bitmaps(const Geometry &g, int npairs, int cus, const LaunchTune &t)
+int coarse_items_in_bitmaps(const Geometry &g, int npairs, int cus, const LaunchTune &t, bool skip_l1)
 {
     const int cn = coarse_levels_used(g, npairs, &t);
     if (npairs < 1 || small_search_used(g, &t) || t.bm_waves != 4 || cn < 1 || cn > 3 || cn >= g.L)
+        return 0;
+    if (skip_l1 && g.L - cn <= 1)  // level 1 is coarse and its gray is not there
         return 0;
     for (int i = 0; i < cn; ++i)
         if (2 * g.lv[g.L - 1 - i].wpr > kWave)

@@ -204,3 +204,32 @@ def test_coarse_levels_inside_the_bitmaps_launch(mtb, n, w, h, L, coarse):
     assert np.array_equal(got["shifts"].cpu().numpy(), want["shifts"])
     assert np.array_equal(got["errs"].cpu().numpy().astype(np.int64), want["errs"])
     assert np.array_equal(got["trace"].cpu().numpy(), alt["trace"].cpu().numpy())
+
+
+def _check_traces(got, imgs, L):
+    want = oracle.align_stack(imgs, L, threads=4)
+    assert np.array_equal(got["shifts"].cpu().numpy(), want["shifts"])
+    assert np.array_equal(got["errs"].cpu().numpy().astype(np.int64), want["errs"])
+    trace = got["trace"].cpu().numpy().astype(np.int64)
+    for k, pair in want["pairs"].items():
+        assert np.array_equal(trace[k], pair["trace"]), f"trace of image {k}"
+
+
+# With few levels the coarse levels reach down to level 1, whose gray is not in
+# the workspace where its bitmaps come from level 0: the workspace's old bytes
+# must not be searched instead.
+@pytest.mark.parametrize("n,w,h,L", [(2, 640, 480, 2), (2, 800, 600, 2), (2, 640, 480, 3), (2, 900, 700, 3),
+                                     (2, 1024, 768, 3), (2, 1024, 768, 4), (2, 1100, 700, 4), (3, 1000, 700, 4),
+                                     (3, 1000, 700, 5)])
+@pytest.mark.parametrize("l1", [0, 1])
+def test_coarse_levels_where_level_1_comes_from_level_0(mtb, n, w, h, L, l1):
+    imgs, _, _ = synth.make_stack(w, h, n, 12, 900 + w + L, 1 << (L - 1), sat_frac=0.05)
+    ws = torch.full((mtb.mtb_stack_workspace_bytes(n, w, h, L),), 173, dtype=torch.uint8, device=DEV)
+    mtb.mtb_tune_reset()
+    mtb.mtb_set_shape(n, w, h, 3 * w, L, {"small_search": 0, "level1_from_level0": l1})
+    try:
+        got = mtb.mtb_align_stack([_view(im, 0, 0) for im in imgs], L, workspace=ws, trace=True)
+    finally:
+        mtb.mtb_tune_reset()
+    torch.cuda.synchronize()
+    _check_traces(got, imgs, L)
