@@ -101,14 +101,14 @@ typedef uint32_t U32u __attribute__((aligned(1)));
 __device__ __forceinline__ void load_rgb16(const uint8_t *rgb, int64_t stride, int x0, int y0, int W, int H,
                                            uint32_t (&q)[4][12])
 {
-    const int nb = 3 * (W - x0);  // bytes from the lane's first pixel to the row's end
-    if (nb <= 0)
+    const int np = W - x0;  // pixels from the lane's first to the row's end: 3 np may pass 2^31
+    if (np <= 0)
         return;
     const uint8_t *row[4];
 #pragma unroll
     for (int rr = 0; rr < 4; ++rr)
         row[rr] = rgb + (int64_t)(y0 + rr < H ? y0 + rr : H - 1) * stride + 3 * (int64_t)x0;
-    if (nb >= 48) {
+    if (np >= 16) {
 #pragma unroll
         for (int rr = 0; rr < 4; ++rr)
 #pragma unroll
@@ -122,6 +122,7 @@ __device__ __forceinline__ void load_rgb16(const uint8_t *rgb, int64_t stride, i
     } else {
         // 3 or more bytes are left.  Where only 3 are, the byte before them
         // belongs to the row too, unless the row is a single pixel.
+        const int nb = 3 * np;
 #pragma unroll
         for (int rr = 0; rr < 4; ++rr)
 #pragma unroll

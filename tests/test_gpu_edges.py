@@ -233,3 +233,29 @@ def test_coarse_levels_where_level_1_comes_from_level_0(mtb, n, w, h, L, l1):
         mtb.mtb_tune_reset()
     torch.cuda.synchronize()
     _check_traces(got, imgs, L)
+
+
+# Rows whose bytes pass 2^31 and 2^32: every pixel's gray and both levels'
+# histograms, against the same integers formed by torch.
+@pytest.mark.parametrize("w,h,L", [(715_827_899, 2, 2), (800_000_003, 1, 1), (1_431_655_783, 1, 1)])
+def test_pyramid_of_very_long_rows(mtb, w, h, L):
+    torch.manual_seed(w)
+    img = torch.randint(0, 256, (h, w, 3), dtype=torch.uint8, device=DEV)
+    lay = mtb.mtb_get_layout(w, h, L)
+    pyr = torch.full((mtb.mtb_pyramid_bytes(w, h, L),), 173, dtype=torch.uint8, device=DEV)
+    mtb.mtb_build_pyramid(img, L, pyramid=pyr)
+    weights = torch.tensor([54, 183, 19], dtype=torch.int32, device=DEV)
+    hist = torch.zeros((L, 256), dtype=torch.int64, device=DEV)
+    step = 1 << 25
+    for x in range(0, w, step):
+        gray = (img[:, x:x + step].to(torch.int32) * weights).sum(2, dtype=torch.int32) >> 8
+        for l in range(L):
+            if l:
+                gray = gray[:, :gray.shape[1] // 2 * 2].reshape(gray.shape[0] // 2, 2, -1, 2).sum((1, 3)) >> 2
+            p, x_l = lay.gray_pitch[l], x >> l
+            for y in range(gray.shape[0]):
+                o = lay.gray_offset[l] + y * p + x_l
+                assert torch.equal(pyr[o:o + gray.shape[1]], gray[y].to(torch.uint8)), f"level {l} from column {x_l}"
+            hist[l] += torch.bincount(gray.reshape(-1), minlength=256)
+    got = pyr[lay.hist_offset:lay.hist_offset + 1024 * L].view(torch.int32).view(L, 256)
+    assert torch.equal(got.to(torch.int64), hist)
