@@ -41,7 +41,7 @@ bool make_geometry(int32_t W, int32_t H, int32_t L, Geometry *g)
         lv.w = W >> l;
         lv.h = H >> l;
         // Rows padded to 128 pixels: gray rows start on 128-byte lines.
-        lv.wpr = 2 * ((lv.w + 127) / 128);
+        lv.wpr = 2 * ((lv.w - 1) / 128 + 1);  // w + 127 may pass 2^31
         lv.gray_pitch = 64 * (int64_t)lv.wpr;
         lv.gray_off = off;
         off = align_up(off + lv.gray_pitch * lv.h, kAlign);

@@ -2603,8 +2603,8 @@ hipError_t launch_zero(const ZeroArgs &a, hipStream_t s)
 hipError_t launch_pyramid(const PyramidArgs &in, int cus, hipStream_t s, int slots_pct, int group_log2)
 {
     PyramidArgs a = in;
-    a.tiles_x = (a.g.W + kTileW - 1) / kTileW;
-    a.tiles_y = (a.g.H + kTileH - 1) / kTileH;
+    a.tiles_x = (a.g.W - 1) / kTileW + 1;  // W + kTileW may pass 2^31
+    a.tiles_y = (a.g.H - 1) / kTileH + 1;
     const int64_t total = (int64_t)a.tiles_x * a.tiles_y * a.n;
     // One round of resident workgroups (scaled by slots_pct); each XCD gets
     // the same number of slots (see k_pyramid), at most one per tile group.

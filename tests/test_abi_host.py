@@ -105,6 +105,12 @@ def test_workspace_sizes(mtb):
     assert mtb.mtb_pair_workspace_bytes(0) == 0 and mtb.mtb_pair_workspace_bytes(17) == 0
 
 
+@pytest.mark.parametrize("w", [2**31 - 1, 2**31 - 127, 2**31 - 128, 2**31 - 255])
+def test_layout_of_the_longest_rows(mtb, w):
+    test_layout_is_consistent(mtb, w, 1, 1)
+    test_layout_is_consistent(mtb, 1, w, 1)
+
+
 @pytest.mark.parametrize("w,h,L", [(0, 5, 1), (5, 0, 1), (10, 10, 0), (10, 10, 5), (1 << 16, 1 << 15, 1)])
 def test_invalid_sizes_rejected(mtb, w, h, L):
     assert mtb.mtb_pyramid_bytes(w, h, L) == 0

@@ -237,7 +237,8 @@ def test_coarse_levels_where_level_1_comes_from_level_0(mtb, n, w, h, L, l1):
 
 # Rows whose bytes pass 2^31 and 2^32: every pixel's gray and both levels'
 # histograms, against the same integers formed by torch.
-@pytest.mark.parametrize("w,h,L", [(715_827_899, 2, 2), (800_000_003, 1, 1), (1_431_655_783, 1, 1)])
+@pytest.mark.parametrize("w,h,L", [(715_827_899, 2, 2), (800_000_003, 1, 1), (1_431_655_783, 1, 1), (2**31 - 200, 1, 1),
+                                   (2**31 - 1, 1, 1)])
 def test_pyramid_of_very_long_rows(mtb, w, h, L):
     torch.manual_seed(w)
     img = torch.randint(0, 256, (h, w, 3), dtype=torch.uint8, device=DEV)
