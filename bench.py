@@ -953,7 +953,7 @@ def main():
         "step_us": {"median": round(step_us[len(step_us) // 2], 1), "min": round(step_us[0], 1),
                     "max": round(step_us[-1], 1), "steps": len(step_us)},
         "e2e_incl_h2d": {"ms_per_step": round(e2e_ms, 3), "MPps": round(mp_total / (e2e_ms / 1e3), 1)},
-        "launch_shape": {"tuned": False, "pyramid_slots_pct": 100, "pyramid_tile_group": 1,
+        "launch_shape": {"tuned": False, "pyramid_slots_pct": 100, "pyramid_tile_group": "built-in rule",
                          "bitmaps_blocks_pct": 100, "bitmaps_waves": 4, "coarse_levels": "built-in rule",
                          "small_search": "built-in rule", "level1_from_level0": "built-in rule",
                          "search_rows": "built-in rule", "search_lanes": "built-in rule"}

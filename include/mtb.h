@@ -276,10 +276,12 @@ mtb_status mtb_align_stack_chained(const uint8_t *const *h_d_rgb, int32_t n, int
  * shape (mtb_launch_shape) fixes:
  *   - the pyramid pass: workgroups as a percentage of one round of the
  *     workgroups the device holds at once, and how many horizontally
- *     adjacent 64x256 tiles a workgroup takes at a time (1, 2 or 4);
- *   - the bitmaps pass: workgroups as a percentage of the built-in number (one
- *     resident round, more for large launch sets), and wavefronts per
- *     workgroup (2, 4 or 8);
+ *     adjacent 64x256 tiles a workgroup takes at a time (1, 2 or 4; without a
+ *     shape two where a launch has between one and two tiles a workgroup,
+ *     else one);
+ *   - the bitmaps pass: workgroups as a percentage of one resident round
+ *     (100: the built-in number, one resident round or for large launch sets
+ *     more), and wavefronts per workgroup (2, 4 or 8);
  *   - the search: how many of the coarsest levels are searched over
  *     exhaustive windows (radius 1, 3, 7, 15, 31 from the coarsest down;
  *     -1: the built-in rule, up to three levels of at most 8192 words of
@@ -310,7 +312,7 @@ mtb_status mtb_align_stack_chained(const uint8_t *const *h_d_rgb, int32_t n, int
  */
 typedef struct mtb_launch_shape {
     int32_t pyramid_slots_pct;  /* 25 .. 400 (default 100) */
-    int32_t pyramid_tile_group; /* 1, 2 or 4 (default 1: two where that gives each slot one group) */
+    int32_t pyramid_tile_group; /* 1, 2 or 4 */
     int32_t bitmaps_blocks_pct; /* 25 .. 100 (default 100) */
     int32_t bitmaps_waves;      /* 2, 4 or 8 (default 4) */
     int32_t coarse_levels;      /* -1 (rule), 0 .. 5 */
@@ -326,7 +328,7 @@ typedef struct mtb_launch_shape {
  * Tunes the launch shape of mtb_align_stack for these images: times whole
  * alignments (median of 7 after a warm-up, HIP events on `stream`) under the
  * built-in shape and under candidates changed one knob at a time (pyramid
- * 50/75/150/200 %, tile groups of 2 and 4, bitmaps 50/75 %, 2 and 8
+ * 50/75/150/200 %, the tile groups the rule would not take, bitmaps 50/75 %, 2 and 8
  * wavefronts, the search by the launches above where one workgroup would
  * take the pair, and unless one workgroup searches: one coarse level fewer
  * or more, and at each fine level every

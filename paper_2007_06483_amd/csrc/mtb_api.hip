@@ -393,9 +393,10 @@ std::string tune_platform()
 // Times candidate shapes for one key by the median of kReps calls of run(t)
 // (HIP events on s, after a warm-up call), changing one knob at a time from
 // the built-in shape and keeping a change only if it is at least 2 % faster.
+// The chosen shape names the tile group that ran, also where the rule gave it.
 // run(t) enqueues a whole call that uses shape t for this key.
 template <typename Run>
-mtb_status tune_one(const Geometry &g, int npairs, int cus, hipStream_t s, Run run, LaunchTune *out_best,
+mtb_status tune_one(const Geometry &g, int n, int npairs, int cus, hipStream_t s, Run run, LaunchTune *out_best,
                     float *out_ms, float *out_default_ms)
 {
     hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -440,7 +441,10 @@ mtb_status tune_one(const Geometry &g, int npairs, int cus, hipStream_t s, Run r
         c.pyr_pct = pct;
         consider(c);
     }
-    for (int gl : {1, 2}) {
+    const int rule_group = pyramid_group_rule(g, n, cus, best.pyr_pct);
+    for (int gl : {0, 1, 2}) {
+        if (gl == rule_group)
+            continue;
         LaunchTune c = best;
         c.pyr_group_log2 = gl;
         consider(c);
@@ -497,6 +501,8 @@ mtb_status tune_one(const Geometry &g, int npairs, int cus, hipStream_t s, Run r
     (void)hipEventDestroy(e1);
     if (st != MTB_OK)
         return st;
+    if (best.pyr_group_log2 < 0)
+        best.pyr_group_log2 = rule_group;
     *out_best = best;
     *out_ms = best_ms;
     *out_default_ms = default_ms;
@@ -1272,7 +1278,7 @@ mtb_status mtb_tune_stack(const uint8_t *const *h_d_rgb, int32_t n, int32_t widt
     make_geometry(width, height, levels, &g);  // valid: the first run checked it
     LaunchTune best;
     float best_ms = 0.f, default_ms = 0.f;
-    st = tune_one(g, n - 1, current_device_cus(), s, run, &best, &best_ms, &default_ms);
+    st = tune_one(g, n, n - 1, current_device_cus(), s, run, &best, &best_ms, &default_ms);
     if (st != MTB_OK)
         return st;
     // The winning shape leaves its results in d_shifts / d_errs as well.
@@ -1518,7 +1524,7 @@ mtb_status mtb_tune_batch(const mtb_batch_item *h_items, int32_t n_items, int32_
         };
         LaunchTune best;
         float ms = 0.f, def = 0.f;
-        st = tune_one(g, group_pairs(u, grp), current_device_cus(), s, run, &best, &ms, &def);
+        st = tune_one(g, grp.images, group_pairs(u, grp), current_device_cus(), s, run, &best, &ms, &def);
         if (st != MTB_OK)
             return st;
         tune_store(key, best);

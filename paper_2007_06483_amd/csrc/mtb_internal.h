@@ -233,8 +233,9 @@ hipError_t launch_kernel(const char *name, void (*k)(A), dim3 grid, dim3 block, 
 
 // Launch shapes a tuner may change (results never depend on them): k_pyramid
 // workgroups as a percentage of one resident round and the tiles of a row a
-// workgroup takes at a time (2^pyr_group_log2); k_bitmaps workgroups as a
-// percentage of one resident round and wavefronts per workgroup; how many of
+// workgroup takes at a time (2^pyr_group_log2; -1: the rule, never in a stored
+// shape); k_bitmaps workgroups as a percentage of one resident round (100: the
+// built-in number) and wavefronts per workgroup; how many of
 // the coarsest levels are searched over exhaustive windows (-1: the rule);
 // and per fine level the rows per stream (0: the rule that keeps the grid
 // within one resident round) and the lanes per row stream (log2, 3 .. 6; 0:
@@ -243,7 +244,7 @@ constexpr int kRowsStep = 4;   // rows per stream come in multiples of this
 constexpr int kRowsMax = 64;
 struct LaunchTune {
     int32_t pyr_pct = 100;
-    int32_t pyr_group_log2 = 0;
+    int32_t pyr_group_log2 = -1;
     int32_t bm_pct = 100;
     int32_t bm_waves = 4;
     int32_t coarse = -1;
@@ -256,8 +257,13 @@ struct LaunchTune {
 // Launch helpers (mtb_kernels.hip).  Each returns the hipError_t of its launches.
 hipError_t launch_zero(const ZeroArgs &a, hipStream_t s);
 hipError_t launch_pyramid(const PyramidArgs &a, int device_cus, hipStream_t s, int slots_pct = 100,
-                          int group_log2 = 0);
+                          int group_log2 = -1);
+// The tile group (log2) launch_pyramid takes without one.
+int pyramid_group_rule(const Geometry &g, int n, int device_cus, int slots_pct);
 hipError_t launch_bitmaps(const BitmapArgs &a, int device_cus, hipStream_t s, int blocks_pct = 100, int waves = 4);
+// Its workgroups (of `waves` wavefronts) for `total` items where `round` are
+// resident at once: at most blocks_pct % of a round, or for 100 the built-in number.
+int64_t bitmaps_blocks(int64_t total, int waves, int64_t round, int blocks_pct);
 hipError_t launch_apply(const ApplyArgs &a, int device_cus, hipStream_t s);
 // The byte-map comparison path: T/E as 255/0 bytes, and the search over them.
 hipError_t launch_bytemaps(const BitmapArgs &a, int device_cus, hipStream_t s);

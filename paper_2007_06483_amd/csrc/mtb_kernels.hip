@@ -2600,23 +2600,38 @@ hipError_t launch_zero(const ZeroArgs &a, hipStream_t s)
     return launch_kernel("k_zero", k_zero, dim3(blocks, a.count), dim3(256), s, a);
 }
 
+// Tiles of each XCD's share of a k_pyramid launch over n images, and the slots
+// (workgroups) of each XCD: one round of resident workgroups, scaled by slots_pct.
+void pyramid_share(const Geometry &g, int n, int cus, int slots_pct, int64_t *share, int64_t *slots)
+{
+    const int64_t tiles_x = (g.W - 1) / kTileW + 1, tiles_y = (g.H - 1) / kTileH + 1;  // W + kTileW may pass 2^31
+    *share = (tiles_x * tiles_y * n + kXcds - 1) / kXcds;
+    *slots = (int64_t)cus * resident_per_cu<k_pyramid>() * slots_pct / (100 * kXcds);
+}
+
+// The built-in tile group (log2).  Between one and two tiles a slot, fewer
+// workgroups of two neighbouring tiles each: some have two in any case, and
+// these share cache lines and flush once (4 x 2560x1440 53.0 -> 50.1 us, 3 x
+// 3000x2000 62.0 -> 59.8, 5 x 2449x1633 62.5 -> 61.2; at 2.9 and 3.9 tiles a slot
+// even, beyond worse).
+int pyramid_group_rule(const Geometry &g, int n, int cus, int slots_pct)
+{
+    int64_t share, slots;
+    pyramid_share(g, n, cus, slots_pct, &share, &slots);
+    return share > slots && share <= 2 * slots;
+}
+
 hipError_t launch_pyramid(const PyramidArgs &in, int cus, hipStream_t s, int slots_pct, int group_log2)
 {
     PyramidArgs a = in;
-    a.tiles_x = (a.g.W - 1) / kTileW + 1;  // W + kTileW may pass 2^31
+    int64_t share, slots;
+    pyramid_share(a.g, a.n, cus, slots_pct, &share, &slots);
+    if (group_log2 < 0)
+        group_log2 = pyramid_group_rule(a.g, a.n, cus, slots_pct);
+    a.tiles_x = (a.g.W - 1) / kTileW + 1;
     a.tiles_y = (a.g.H - 1) / kTileH + 1;
-    const int64_t total = (int64_t)a.tiles_x * a.tiles_y * a.n;
-    // One round of resident workgroups (scaled by slots_pct); each XCD gets
-    // the same number of slots (see k_pyramid), at most one per tile group.
-    const int64_t share = (total + kXcds - 1) / kXcds;
-    int64_t slots = (int64_t)cus * resident_per_cu<k_pyramid>() * slots_pct / (100 * kXcds);
-    // Between one and two tiles a slot, fewer workgroups of two neighbouring
-    // tiles each: some have two in any case, and these share cache lines and
-    // flush once (4 x 2560x1440 53.0 -> 50.1 us, 3 x 3000x2000 62.0 -> 59.8, 5 x
-    // 2449x1633 62.5 -> 61.2; at 2.9 and 3.9 tiles a slot even, beyond worse).
-    if (group_log2 == 0 && share > slots && share <= 2 * slots)
-        group_log2 = 1;
     a.group_log2 = group_log2;
+    // Each XCD gets the same number of slots (see k_pyramid), at most one per tile group.
     const int64_t groups = (share + (1 << group_log2) - 1) >> group_log2;
     slots = slots > groups ? groups : (slots < 1 ? 1 : slots);
     a.xcd_tiles = (int32_t)share;
@@ -2710,15 +2725,18 @@ hipError_t launch_search_bytes(SearchArgs a, int cus, hipStream_t s)
 // 2 us faster and quadrants of 6000x4000 2 us slower.
 constexpr int kItemsPerWave = 4;
 
+int64_t bitmaps_blocks(int64_t total, int waves, int64_t round, int blocks_pct)
+{
+    const int64_t blocks = (total + waves - 1) / waves, most = total / (waves * kItemsPerWave);
+    const int64_t cap = blocks_pct < 100 ? round * blocks_pct / 100 : (most > round ? most : round);
+    return blocks > cap ? cap : (blocks < 1 ? 1 : blocks);
+}
+
 template <int kW, bool kPairs, bool kCoarse = false>
 hipError_t launch_bitmaps_w(const BitmapArgs &a, int cus, hipStream_t s, int blocks_pct)
 {
-    const int64_t total = a.chunk_start[a.g.L] * a.n;
-    int64_t blocks = (total + kW - 1) / kW;
     const int64_t round = (int64_t)cus * resident_per_cu<k_bitmaps<kW, kPairs, kCoarse>, 64 * kW>();
-    const int64_t most = total / (kW * kItemsPerWave);
-    const int64_t cap = (most > round ? most : round) * blocks_pct / 100;
-    blocks = (blocks > cap ? cap : (blocks < 1 ? 1 : blocks)) + a.coarse_blocks;
+    const int64_t blocks = bitmaps_blocks(a.chunk_start[a.g.L] * a.n, kW, round, blocks_pct) + a.coarse_blocks;
     return launch_kernel("k_bitmaps", k_bitmaps<kW, kPairs, kCoarse>, dim3((unsigned)blocks), dim3(64 * kW), s, a);
 }
 

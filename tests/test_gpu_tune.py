@@ -136,3 +136,37 @@ def test_tuned_batch_groups_keep_results(mtb):
     want = np.array([oracle.align_pair(r, m, L)["shift"] for r, m, L in items], dtype=np.int32)
     assert np.array_equal(b_sh, want)
     mtb.mtb_tune_reset()
+
+
+def test_a_stored_tile_group_is_the_one_that_runs(mtb):
+    # 1152 tiles for the 768 workgroups a device of 256 compute units holds at
+    # once: the built-in rule takes groups of two there, but a stored shape's
+    # number holds.
+    n, w, h, L = 3, 3000, 2000, 7
+    imgs, d = _stack(n, w, h, 63, 30)
+
+    def blocks_with(shape):
+        mtb.mtb_tune_reset()
+        if shape:
+            mtb.mtb_set_shape(n, w, h, 3 * w, L, shape)
+        got = _run(mtb, d, L)
+        return mtb.mtb_test_last_pyramid()[0], got
+
+    rule, want = blocks_with(None)
+    seen = {}
+    for group in (1, 2, 4):
+        seen[group], got = blocks_with({"pyramid_tile_group": group})
+        assert mtb.mtb_tuned_shape(n, w, h, 3 * w, L)["pyramid_tile_group"] == group
+        for a, b in zip(want, got):
+            assert np.array_equal(a, b)
+    assert seen[1] > seen[2] > seen[4] and rule == seen[2]
+    # A tuned shape names what was timed: stored again, it runs the same launch.
+    mtb.mtb_tune_reset()
+    shape = mtb.mtb_tune_stack(d, L)
+    _run(mtb, d, L)
+    tuned = mtb.mtb_test_last_pyramid()[0]
+    again, got = blocks_with(shape)
+    assert again == tuned
+    for a, b in zip(want, got):
+        assert np.array_equal(a, b)
+    mtb.mtb_tune_reset()

@@ -97,3 +97,17 @@ def test_tuner_argument_checks():
         bad[i] = v
         assert L.mtb_tune_stack(*bad) in (1, 2), (i, v)   # MTB_ERR_INVALID_ARG or MTB_ERR_WORKSPACE
     assert mtb.mtb_tuned_shape(2, 64, 48, 192, 3) is None
+
+
+@pytest.mark.parametrize("total,waves", [(1, 4), (7000, 4), (100_000, 2), (100_000, 4), (100_000, 8), (1_000_000, 4)])
+def test_bitmaps_workgroups(total, waves):
+    # A percentage below 100 is one of a resident round, whatever the launch
+    # set's size; 100 is the built-in number, at least one round where the
+    # items suffice and never fewer than four items a wavefront beyond it.
+    blocks = mtb.lib()["_ZN3mtb14bitmaps_blocksElili"]  # mtb::bitmaps_blocks(int64_t, int, int64_t, int)
+    blocks.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_int64, ctypes.c_int]
+    blocks.restype = ctypes.c_int64
+    round_, one_item = 1792, -(-total // waves)
+    for pct in (25, 50, 75, 99):
+        assert blocks(total, waves, round_, pct) == min(one_item, round_ * pct // 100)
+    assert blocks(total, waves, round_, 100) == min(one_item, max(round_, total // (4 * waves)))
