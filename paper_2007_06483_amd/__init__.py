@@ -575,11 +575,12 @@ def mtb_apply_shifts(images, shifts: torch.Tensor, fill: int = MTB_FILL_ZERO, ou
         raise ValueError("shifts must be a contiguous int32 device tensor of shape (n, 2)")
     if out is None:
         out = [torch.empty((H, W, 3), dtype=torch.uint8, device=images[0].device) for _ in range(n)]
-    ow, oh, ostride = _stack_geometry(out, "outputs must match the inputs' size and share a stride", same_device=False)
+    placed = list(out)  # any collection
+    ow, oh, ostride = _stack_geometry(placed, "outputs must match the inputs' size and share a stride", same_device=False)
     if (ow, oh) != (W, H):
         raise ValueError("outputs must match the inputs' size and share a stride")
     ins = (ctypes.c_void_p * n)(*[im.data_ptr() for im in images])
-    outs = (ctypes.c_void_p * n)(*[o.data_ptr() for o in out])
+    outs = (ctypes.c_void_p * n)(*[o.data_ptr() for o in placed])
     _check("mtb_apply_shifts",
            lib().mtb_apply_shifts(ins, n, W, H, stride, _ptr(shifts), int(fill), outs, ostride,
                                   _stream(stream)))

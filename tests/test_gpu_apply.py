@@ -90,3 +90,15 @@ def test_apply_stack_shifts_full_size(mtb):
         for k in (0, 3, 6):
             want = oracle.apply_shift(imgs[k], int(shifts[k][0]), int(shifts[k][1]), fill)
             assert np.array_equal(outs[k].cpu().numpy(), want), (k, fill)
+
+
+def test_outputs_in_any_collection(mtb):
+    # `out` may be any collection of tensors, not only one that can be indexed.
+    imgs = [np.random.default_rng(k).integers(0, 256, (31, 47, 3), dtype=np.uint8) for k in range(3)]
+    shifts = [(0, 0), (3, -2), (-5, 4)]
+    sh = torch.tensor(shifts, dtype=torch.int32, device=DEV)
+    outs = {k: _dev(np.zeros_like(im)) for k, im in enumerate(imgs)}
+    got = mtb.mtb_apply_shifts([_dev(im) for im in imgs], sh, out=outs.values())
+    torch.cuda.synchronize()
+    for im, o, (dx, dy) in zip(imgs, got, shifts):
+        assert np.array_equal(o.cpu().numpy(), oracle.apply_shift(im, dx, dy, 0))
