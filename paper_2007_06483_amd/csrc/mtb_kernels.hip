@@ -653,7 +653,7 @@ __device__ __forceinline__ int coarse_surface_offset(int i)
 
 // Column width (log2, in dwords) and row slabs of a coarse level handled by
 // 256-lane workgroups: CW = 2^cw_log2 columns x 256 / CW row streams, each
-// stream scoring 8 rows of a slab.
+// stream scoring kCoarseRows rows of a slab.
 __host__ __device__ __forceinline__ int coarse_cw_log2(const LevelGeom &lv)
 {
     int c = 0;
@@ -825,29 +825,30 @@ __device__ __forceinline__ uint32_t mark_bits8(uint32_t m0, uint32_t m1)
     return __builtin_amdgcn_udot4(m1, 0x80402010u, __builtin_amdgcn_udot4(m0, 0x08040201u, 0u, false), false);
 }
 
-// T and E bits of 4 kDwords consecutive pixels d (byte b of d[k] = pixel 4k + b).
-template <int kDwords, bool kLowT, bool kLowHi, bool kLowLo>
-__device__ __forceinline__ void te_bits_of(const uint32_t *d, const Thresholds &c, uint32_t &tw, uint32_t &ew)
+// T and E bits of 32 pixels from the marks of each eight (mark_bits8).
+__device__ __forceinline__ void gather_marks(const uint32_t (&t)[4], const uint32_t (&band)[4], uint32_t &tw, uint32_t &ew)
 {
-    uint32_t ta[kDwords / 2], ba[kDwords / 2];
-#pragma unroll
-    for (int k = 0; k < kDwords; k += 2) {
-        uint32_t t0, t1, b0, b1;
-        te_marks<kLowT, kLowHi, kLowLo>(d[k], c, t0, b0);
-        te_marks<kLowT, kLowHi, kLowLo>(d[k + 1], c, t1, b1);
-        ta[k / 2] = mark_bits8(t0, t1);
-        ba[k / 2] = mark_bits8(b0, b1);
-    }
-    if constexpr (kDwords == 8) {
-        tw = ((ta[0] + (ta[1] << 8) + (ta[2] << 16)) >> 7) | (ta[3] << 17);
-        ew = ~(((ba[0] + (ba[1] << 8) + (ba[2] << 16)) >> 7) | (ba[3] << 17));
-    } else {
-        tw = (ta[0] + (ta[1] << 8)) >> 7;
-        ew = ~((ba[0] + (ba[1] << 8)) >> 7);
-    }
+    tw = ((t[0] + (t[1] << 8) + (t[2] << 16)) >> 7) | (t[3] << 17);
+    ew = ~(((band[0] + (band[1] << 8) + (band[2] << 16)) >> 7) | (band[3] << 17));
 }
 
-// Eight dwords' T and E bits with the cases picked at run time.
+// T and E bits of 32 consecutive pixels d (byte b of d[k] = pixel 4k + b).
+template <bool kLowT, bool kLowHi, bool kLowLo>
+__device__ __forceinline__ void te_bits_of(const uint32_t *d, const Thresholds &c, uint32_t &tw, uint32_t &ew)
+{
+    uint32_t ta[4], ba[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        uint32_t t0, t1, b0, b1;
+        te_marks<kLowT, kLowHi, kLowLo>(d[2 * k], c, t0, b0);
+        te_marks<kLowT, kLowHi, kLowLo>(d[2 * k + 1], c, t1, b1);
+        ta[k] = mark_bits8(t0, t1);
+        ba[k] = mark_bits8(b0, b1);
+    }
+    gather_marks(ta, ba, tw, ew);
+}
+
+// The same with the cases picked at run time, without a branch.
 __device__ __forceinline__ void te_bits_any(const uint32_t *d, const Thresholds &c, uint32_t &tw, uint32_t &ew)
 {
     uint32_t ta[4], ba[4];
@@ -859,18 +860,16 @@ __device__ __forceinline__ void te_bits_any(const uint32_t *d, const Thresholds 
         ta[k] = mark_bits8(t0, t1);
         ba[k] = mark_bits8(b0, b1);
     }
-    tw = ((ta[0] + (ta[1] << 8) + (ta[2] << 16)) >> 7) | (ta[3] << 17);
-    ew = ~(((ba[0] + (ba[1] << 8) + (ba[2] << 16)) >> 7) | (ba[3] << 17));
+    gather_marks(ta, ba, tw, ew);
 }
 
-template <int kDwords>
 __device__ __forceinline__ void te_bits(const uint32_t *d, const Thresholds &c, uint32_t &tw, uint32_t &ew)
 {
     switch (c.nlow) {
-    case 0: te_bits_of<kDwords, false, false, false>(d, c, tw, ew); break;
-    case 1: te_bits_of<kDwords, false, false, true>(d, c, tw, ew); break;
-    case 2: te_bits_of<kDwords, true, false, true>(d, c, tw, ew); break;
-    default: te_bits_of<kDwords, true, true, true>(d, c, tw, ew); break;
+    case 0: te_bits_of<false, false, false>(d, c, tw, ew); break;
+    case 1: te_bits_of<false, false, true>(d, c, tw, ew); break;
+    case 2: te_bits_of<true, false, true>(d, c, tw, ew); break;
+    default: te_bits_of<true, true, true>(d, c, tw, ew); break;
     }
 }
 
@@ -917,7 +916,7 @@ __device__ __forceinline__ void walk_chunks(const BitmapArgs &a, int64_t c0, int
             load_chunk(a, p, lane, v0, v1);
         }
         uint32_t tw, ew;
-        te_bits<8>(d, th, tw, ew);
+        te_bits(d, th, tw, ew);
         // Bits past the level width are zero: lane i holds half-word i % 2 of
         // word w0 + i / 2, whose pixels start at column 64 * ((w0 + i / 2) mod wpr).
         int col = ccol0 + (lane >> 1);
@@ -1065,7 +1064,7 @@ __device__ __forceinline__ void walk_units(const BitmapArgs &a, int64_t c0, int6
         uint32_t g1[2];
         level1_gray(d, g1);
         uint32_t tw, ew;
-        te_bits<8>(d, th0, tw, ew);
+        te_bits(d, th0, tw, ew);
         pair_unit(a, ci, cj, cs, lane, g1, tw, ew, th1);
     }
 }
