@@ -260,3 +260,23 @@ def test_pyramid_of_very_long_rows(mtb, w, h, L):
             hist[l] += torch.bincount(gray.reshape(-1), minlength=256)
     got = pyr[lay.hist_offset:lay.hist_offset + 1024 * L].view(torch.int32).view(L, 256)
     assert torch.equal(got.to(torch.int64), hist)
+
+
+# The same levels' traces (every candidate's error, not the winners' alone)
+# against the oracle: by the built-in rule, and in row streams of given rows,
+# which k_search_fine takes at every level.
+@pytest.mark.parametrize("n,w,h,L", [(2, 1300, 1250, 5), (2, 2000, 1030, 6), (2, 2049, 2051, 6), (3, 700, 2901, 6),
+                                     (9, 640, 403, 5), (5, 1111, 777, 6), (2, 129, 4000, 5), (32, 300, 331, 4),
+                                     (5, 8485, 300, 4)])
+@pytest.mark.parametrize("rows", [0, 4, 24])
+@pytest.mark.parametrize("coarse", [-1, 0])
+def test_fine_levels_traces(mtb, n, w, h, L, rows, coarse):
+    imgs, _, _ = synth.make_stack(w, h, n, 12, 500 + w + n, min(1 << (L - 1), min(w, h) // 4), sat_frac=0.05)
+    mtb.mtb_tune_reset()
+    mtb.mtb_set_shape(n, w, h, 3 * w, L, {"small_search": 0, "coarse_levels": coarse, "search_rows": [rows] * 16})
+    try:
+        got = mtb.mtb_align_stack([_view(im, 0, 0) for im in imgs], L, trace=True)
+    finally:
+        mtb.mtb_tune_reset()
+    torch.cuda.synchronize()
+    _check_traces(got, imgs, L)
