@@ -2762,15 +2762,18 @@ hipError_t launch_bitmaps(const BitmapArgs &a, int cus, hipStream_t s, int block
 // The built-in rule searches the i-th coarsest level exhaustively when i < 3,
 // its window rows stay cheap for one workgroup (at most kCoarseDwords dwords)
 // and its whole window over every pair is worth the launch it saves (at most
-// kCoarseCells dwords times shifts: 9 x 8485x5657, 12.7 Mi at its third level,
-// 601 us a call with it and 593 without; 7 x 6000x4000, 3.9 Mi, 234 and 236).
+// kCoarseCells dwords times shifts).  Stacks of 6000x4000 with the third level
+// and without it, the best form of each: 5 images (2.6 Mi) 178.2 and 180.2 us, 7
+// (3.9) 233.1 and 233.6, 8 (4.5) 263.4 and 263.0, 10 (5.8) 319.6 and 317.3, 13
+// (7.7) 405.9 and 401.3; of 5000x3333, 4096x3072 and 8485x5657 the two are even
+// between 3.0 and 4.3 Mi.
 // The windows of radius 15 and 31 (i = 3, 4) are taken only when a launch
 // shape asks for them: on a mix of small stacks they cost more than the fine
 // launches they replace, and pairs small enough to gain from them are searched
 // by one workgroup instead.
 constexpr int64_t kCoarseDwords = 8192;
 constexpr int kCoarseRule = 3;
-constexpr int64_t kCoarseCells = 8 << 20;
+constexpr int64_t kCoarseCells = 4 << 20;
 
 int coarse_level_count(const Geometry &g, int npairs)
 {

@@ -111,3 +111,14 @@ def test_bitmaps_workgroups(total, waves):
     for pct in (25, 50, 75, 99):
         assert blocks(total, waves, round_, pct) == min(one_item, round_ * pct // 100)
     assert blocks(total, waves, round_, 100) == min(one_item, max(round_, total // (4 * waves)))
+
+
+@pytest.mark.parametrize("n,w,h,want", [(2, 6000, 4000, 3), (7, 6000, 4000, 3), (8, 6000, 4000, 2), (32, 6000, 4000, 2),
+                                        (12, 4096, 3072, 3), (14, 4096, 3072, 2), (32, 1000, 700, 3)])
+def test_third_coarse_level_by_its_work(n, w, h, want):
+    # Exhaustive levels of the built-in rule at seven levels: the third while its
+    # words times shifts, over all pairs, are at most 2^22.
+    L = mtb.lib()
+    geometry = ctypes.create_string_buffer(1 << 14)
+    assert L["_ZN3mtb13make_geometryEiiiPNS_8GeometryE"](w, h, 7, geometry)
+    assert L["_ZN3mtb18coarse_level_countERKNS_8GeometryEi"](geometry, n - 1) == want
