@@ -166,8 +166,8 @@ constexpr int kDefer = 8;
 // contiguous bytes), and the next tile's RGB is loaded while the current one
 // is processed, whatever the rows' alignment.
 //
-// Bound by the HBM stream on large launch sets (7 x 6000x4000: 138 us for 686
-// MB, 0.92 of the rate a plain kernel streams the same mix of reads and writes
+// Bound by the HBM stream on large launch sets (7 x 6000x4000: 140 us for 686
+// MB, 0.90 of the rate a plain kernel streams the same mix of reads and writes
 // at), by latency on small ones (one 1920x1080 image 12 us).  What it took:
 //  - One load path for every alignment, with the loads of the next tile in
 //    flight: rows at odd addresses cost no more than the cache lines they
@@ -2610,9 +2610,12 @@ void pyramid_share(const Geometry &g, int n, int cus, int slots_pct, int64_t *sh
 
 // The built-in tile group (log2).  Between one and two tiles a slot, fewer
 // workgroups of two neighbouring tiles each: some have two in any case, and
-// these share cache lines and flush once (4 x 2560x1440 53.0 -> 50.1 us, 3 x
-// 3000x2000 62.0 -> 59.8, 5 x 2449x1633 62.5 -> 61.2; at 2.9 and 3.9 tiles a slot
-// even, beyond worse).
+// these share cache lines and flush once.  Call times with two against one over
+// 43 sets of one to 32 images in that range: 24 faster (4 x 2592x1944 66.9 -> 61.0
+// us, 3 x 3000x2000 66.5 -> 64.2, 5 x 2449x1633 64.4 -> 62.1), 11 within half a
+// percent, 8 slower (1 x 5000x3500 37.8 -> 39.1, 8 x 1600x1200 56.3 -> 58.2, 2 x
+// 3600x2400 60.5 -> 61.6, with no rule that tells them apart), 1.5 % in the mean;
+// at 2.9 and 3.9 tiles a slot even, beyond worse.
 int pyramid_group_rule(const Geometry &g, int n, int cus, int slots_pct)
 {
     int64_t share, slots;
@@ -2719,9 +2722,11 @@ hipError_t launch_search_bytes(SearchArgs a, int cus, hipStream_t s)
 // leave each wavefront this many.  Workgroups started in order keep the device
 // on one front of addresses and even out the compute units; a wavefront's
 // start (two median scans) costs about an item.  With one round whatever the
-// size, 9 x 8485x5657 (45 items) took 23 us longer and 7 x 6000x4000 (14) 2-3;
-// 2.3 items each made 7 x 3001x1999 1 us slower, and three each 7 x 6000x4000
-// 2 us faster and quadrants of 6000x4000 2 us slower.
+// size, 9 x 8485x5657 (45 items) took 23 us longer and 7 x 6000x4000 (14) 2-3.
+// Three, four and six items each: 5 x 6000x4000 177.5, 178.2 and 177.9 us, 7 x
+// 231.2, 233.2 and 234.3, 12 x 375.1, 379.6 and 382.1, 7 x 4096x3072 139.5, 138.7
+// and 141.3, 20 x 322.6, 322.8 and 325.5, 8 x 3000x2000 91.3, 89.8 and 89.8: six
+// gains nowhere, three gives large sets what it takes from small ones.
 constexpr int kItemsPerWave = 4;
 
 int64_t bitmaps_blocks(int64_t total, int waves, int64_t round, int blocks_pct)
@@ -2845,6 +2850,11 @@ int coarse_levels_used(const Geometry &g, int npairs, const LaunchTune *t)
 
 bool small_search_fits(const Geometry &g) { return 2 * (g.med_off - kAlign) <= kSmallLdsBytes; }
 
+// Wherever a pair fits, one workgroup is as fast as the launches or faster, for
+// one pair or 31.  A call of two and of 32 images with it and without: 160x120 27.6
+// against 31.0 us and 33.4 against 39.6, 320x240 29.7 against 31.3 and 37.0 against
+// 41.2, 512x384 31.4 against 31.6 and 41.4 against 44.3, 640x400, about the limit,
+// 36.4 against 37.1 and 52.4 against 52.4.
 bool small_search_used(const Geometry &g, const LaunchTune *t)
 {
     return (!t || t->small != 0) && small_search_fits(g);
@@ -2864,9 +2874,12 @@ int coarse_item_count(const Geometry &g, int cn)
     return items;
 }
 
-// More coarse workgroups than this a compute unit are a launch of their own: 9 x
-// 8485x5657 has 1632, and taking them along made it 7 us slower; the 420 of 7 x
-// 6000x4000 still pay.
+// More coarse workgroups than this a compute unit are a launch of their own.
+// Small sets of many pairs, riding and on their own: 10 x 4096x3072 (360
+// workgroups) 180.9 and 184.9 us, 7 x 6000x4000 (420) 233.1 and 236.9, 20 x
+// 1000x700 (475) 65.4 and 65.0, 24 x 1500x1000 (575) 93.8 and 93.3, 32 x 1000x700
+// (775) 85.7 and 82.2; large sets, which at such counts have two levels, gained
+// up to about 840.
 constexpr int kCoarseBlocksPerCu = 2;
 
 int coarse_items_in_bitmaps(const Geometry &g, int npairs, int cus, const LaunchTune &t, bool skip_l1)
